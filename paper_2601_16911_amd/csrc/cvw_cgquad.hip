@@ -532,7 +532,7 @@ cvw_status cgquad_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const
                       ? cgq_cell_p<1>(m, ms, prm->flux, mode, u, cand, pg, rcell, gamma, alpha, status, s)
                       : cgq_cell_p<2>(m, ms, prm->flux, mode, u, cand, pg, rcell, gamma, alpha, status, s);
   if (st != CVW_OK) return st;
-  if (mode != MODE_SENSOR)
+  if (mode != MODE_SENSOR && R)      // R null: the caller takes the element rows
     hipLaunchKernelGGL(cg_assemble_kernel, dim3(nblk(m->ndof, 256)), dim3(256), 0, s, rcell, R, m->d_dof_ptr,
                        m->d_dof_ent, m->ndof);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;

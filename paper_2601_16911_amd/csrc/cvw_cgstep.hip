@@ -1,57 +1,169 @@
-// Time stepping for the CG paths and the 1D DG path.
+// Time stepping for the CG paths (the DG paths update the state in their cell
+// kernels).
 //
-// CG (Sec. 2.1, eq. sdstab): the stage needs L = -M^{-1} R with the
-// consistent global mass matrix M.  M is inverted by a preconditioned
-// conjugate gradient iteration that stays on the device: its scalars live in
-// a small device array, each kernel reads them, and once the preconditioned
-// residual has dropped below the tolerance every later kernel of the fixed
-// launch sequence returns at once.  No host synchronisation, so a stage can
-// be captured in a graph.  Preconditioner: the inverse row sums of M (the
-// integrals of the nodal basis functions; positive for Gauss-Lobatto nodes).
-// Dot products are reduced in float64 in a fixed order (deterministic).  On
-// a line (segments) the same iteration runs inside one workgroup.
+// The stage needs L = -M^{-1} R with the consistent global mass matrix M (Sec.
+// 2.1, eq. sdstab).
 //
-// 1D DG: Gauss nodes with the (p+1)-point Gauss rule make the element mass
-// exactly diagonal, so the stage divides by it directly.
+// Quadrilaterals: a preconditioned conjugate gradient iteration that stays on
+// the device.  Its scalars live in a small device array or are formed by every
+// block from the block partials, and once the preconditioned residual has dropped
+// below the tolerance every later kernel of the launch sequence returns at once;
+// the sequence is as long as the mesh's spectrum allows an iteration to last.  No
+// host synchronisation, so a stage can be captured in a graph.  Preconditioner:
+// the inverse row sums of M (the integrals of the nodal basis functions; positive
+// for Gauss-Lobatto nodes).  Dot products are reduced in float64 in a fixed order
+// (deterministic).
+//
+// Lines: a direct solve at low degree, the same iteration inside one workgroup
+// per variable at high degree.
 #include "cvw_device.h"
+
+#include <algorithm>
+#include <cmath>
 
 namespace cvw {
 
-enum { S_RZ = 0, S_PAP = 1, S_RZ0 = 2, S_ALPHA = 3, S_BETA = 4, S_DONE = 5, S_TOL2 = 6, S_ITER = 7 };
+enum { S_RZ = 0, S_RZ_ODD = 1, S_RZ0 = 2, S_ALPHA = 3, S_BETA = 4, S_DONE = 5, S_TOL2 = 6, S_NOX = 7 };
 constexpr int PCG_THREADS = 256;
 
 __device__ __forceinline__ bool pcg_done(const double* S) { return S[S_DONE] != 0.0; }
 
-// block sum of one double per thread (PCG_THREADS threads); result valid in every thread
-__device__ __forceinline__ double block_sum(double v, double* sh) {
+// sum of one double per thread over N threads in the order of a halving tree
+// (s = N / 2, ..., 1: thread t adds t + s); the last six levels lie inside the
+// first wave.  Result valid in every thread.
+template <int N>
+__device__ __forceinline__ double tree_sum(double v, double* sh) {
+  __syncthreads();
   sh[threadIdx.x] = v;
   __syncthreads();
 #pragma unroll
-  for (int s = PCG_THREADS / 2; s > 0; s >>= 1) {
+  for (int s = N / 2; s > 64; s >>= 1) {
     if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
     __syncthreads();
   }
+  if (threadIdx.x < 64) {
+    v = sh[threadIdx.x] + sh[threadIdx.x + 64];
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s, 64);
+    if (threadIdx.x == 0) sh[0] = v;
+  }
+  __syncthreads();
   return sh[0];
 }
+// sum of the nb block partials (fixed order)
+__device__ __forceinline__ double partial_sum(const double* __restrict__ part, int nb, double* sh) {
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < nb; i += PCG_THREADS) acc += part[i];
+  return tree_sum<PCG_THREADS>(acc, sh);
+}
 
-// ycell_e = M_e x_e on bilinear quadrilaterals; the (p+1)^2 Gauss rule
-// integrates phi_i phi_j |det J| exactly (degree 2p + 1 per direction)
-template <int P>
-__global__ __launch_bounds__(128) void cgq_mass_kernel(const float* __restrict__ x, float* __restrict__ ycell,
-                                                       const int32_t* __restrict__ cdof, const float* __restrict__ geo,
-                                                       const CGTables* __restrict__ tab, int64_t E,
-                                                       const double* __restrict__ S) {
+// ---------------------------------------------------------------------------
+// Conjugate gradients on bilinear quadrilaterals.  The work is small (65 k cells,
+// 262 k DOFs at 256 x 256 Q2: 20 MB and 20 MFLOP per iteration), the time is
+// launches (3-4 us each on the host) and dependent reads.  So there are no launches
+// for the direction and the scalars (every block sums the partials itself), and
+// the sequence is as long as the mesh's spectrum allows an iteration to last (25
+// instead of always 64).  An iteration is
+//   cells:  beta from the partials of r.z; y_e = M_e p with the new direction
+//           p = z + beta p formed at the cell's nodes on the way in;
+//   gather: p at the DOF, Ap = sum of the y_e, partials of p.Ap;
+//   update: alpha from those partials, x, r, z, partials of r.z;
+// or, up to PCG_APPLY_PARTIALS partials, two launches:
+//   apply:  cells and gather in one, every DOF evaluating its rows of its cells;
+//   update.
+// Apply has four times the vector memory instructions (12.7 us at 262 k DOFs against
+// 4.4 + 3.3 us for cells and gather), but where a kernel takes less than its launch
+// one launch less is what counts.  Above PCG_FUSED_PARTIALS partials summing them
+// in every block would cost more than a launch of its own.  Every sum keeps its
+// order: all variants give the same bits.  A step (three stages) at 256 x 256 Q2:
+// 3371 us with six launches per iteration, 980 us now; at 31 x 27: 3591 us and
+// 697 us; at 500 x 400: 3832 us and 2088 us.
+// ---------------------------------------------------------------------------
+constexpr int PCG_APPLY_PARTIALS = 1024, PCG_FUSED_PARTIALS = 4096;
+
+// R_I = sum of the element rows sharing I (ascending (cell, node) order), r = R,
+// z = D R; block partial of r . z
+__global__ __launch_bounds__(PCG_THREADS) void pcg_init_kernel(const float* __restrict__ rcell,
+                                                               const float* __restrict__ dinv, float* __restrict__ r,
+                                                               float2* __restrict__ pz, double* __restrict__ part,
+                                                               const int32_t* __restrict__ dptr,
+                                                               const int32_t* __restrict__ dent, int64_t n,
+                                                               double* __restrict__ S, double tol2) {
+  __shared__ double sh[PCG_THREADS];
+  const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    S[S_DONE] = 0.0;
+    S[S_TOL2] = tol2;
+  }
+  double d = 0.0;
+  if (i < n) {
+    float bi = 0.0f;
+    for (int it = dptr[i]; it < dptr[i + 1]; ++it) bi += rcell[dent[it]];   // ent = cell * nloc + local node
+    const float zi = dinv[i] * bi;
+    r[i] = bi;
+    pz[i] = make_float2(0.0f, zi);
+    d = static_cast<double>(bi) * static_cast<double>(zi);
+  }
+  const double s = tree_sum<PCG_THREADS>(d, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+// The recurrence at the start of iteration it, from rz = r.z: rz0, beta, done (a
+// zero right-hand side, or the tolerance met); block 0 writes it for the launches
+// behind.  false: done.
+template <bool FIRST>
+__device__ __forceinline__ bool pcg_recur(double rz, double* S, int it, float& beta) {
+  const double b = FIRST ? 0.0 : rz / S[(it & 1) ? S_RZ : S_RZ_ODD];
+  const bool done = FIRST ? !(rz > 0.0) : !(rz > S[S_TOL2] * S[S_RZ0]);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    S[(it & 1) ? S_RZ_ODD : S_RZ] = rz;
+    S[S_BETA] = b;
+    if (FIRST) {
+      S[S_RZ0] = rz;
+      S[S_NOX] = done ? 1.0 : 0.0;
+    }
+    if (done) S[S_DONE] = 1.0;
+  }
+  beta = static_cast<float>(b);
+  return !done;
+}
+
+// p = z + beta p (FIRST: p = z) at the cell's nodes and y = M_e p; the (p+1)^2 Gauss
+// rule integrates phi_i phi_j |det J| exactly (degree 2p + 1 per direction).
+// FUSED: v = r.z from its partials; its recurrence (rz0, done, beta) is written
+// for the launches behind by block 0.
+template <int P, bool FIRST, bool FUSED>
+__global__ __launch_bounds__(PCG_THREADS) void pcg_cells_kernel(const float2* __restrict__ pz, float* __restrict__ ycell,
+                                                                const double* __restrict__ rz_part, int nb,
+                                                                const int32_t* __restrict__ cdof,
+                                                                const float* __restrict__ geo,
+                                                                const CGTables* __restrict__ tab, int64_t E, double* S,
+                                                                int it) {
   constexpr int N1 = P + 1, NLOC = N1 * N1;
+  __shared__ double sh[PCG_THREADS];
   if (pcg_done(S)) return;
-  const int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+  const int64_t e = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x, ec = e < E ? e : E - 1;
+  int I[NLOC];
+  float2 v[NLOC];
+#pragma unroll
+  for (int j = 0; j < NLOC; ++j) I[j] = cdof[j * E + ec];
+#pragma unroll
+  for (int j = 0; j < NLOC; ++j) v[j] = pz[I[j]];
+  const Geo G = load_geo(geo, ec);
+  float beta = 0.0f;
+  if constexpr (FUSED) {
+    const double rz = partial_sum(rz_part, nb, sh);
+    if (!pcg_recur<FIRST>(rz, S, it, beta)) return;
+  } else if constexpr (!FIRST) {
+    beta = static_cast<float>(S[S_BETA]);
+  }
   if (e >= E) return;
   float xe[NLOC], y[NLOC];
 #pragma unroll
   for (int j = 0; j < NLOC; ++j) {
-    xe[j] = x[cdof[e * NLOC + j]];
+    xe[j] = FIRST ? v[j].y : fmaf(beta, v[j].x, v[j].y);
     y[j] = 0.0f;
   }
-  const Geo G = load_geo(geo, e);
 #pragma unroll
   for (int qy = 0; qy < N1; ++qy)
 #pragma unroll
@@ -71,94 +183,157 @@ __global__ __launch_bounds__(128) void cgq_mass_kernel(const float* __restrict__
         for (int a = 0; a < N1; ++a) y[a + N1 * b] = fmaf(tab->Dv[0][qx][a] * tab->Dv[0][qy][b], Wx, y[a + N1 * b]);
     }
 #pragma unroll
-  for (int j = 0; j < NLOC; ++j) ycell[e * NLOC + j] = y[j];
+  for (int j = 0; j < NLOC; ++j) ycell[j * E + e] = y[j];
 }
 
-// Ap_I = sum of the element entries sharing I (ascending (cell, node) order);
-// block partial of p . Ap
-template <typename Real>
-__global__ __launch_bounds__(PCG_THREADS) void pcg_gather_dot_kernel(const Real* __restrict__ ycell,
-                                                                     const Real* __restrict__ p, Real* __restrict__ Ap,
-                                                                     double* __restrict__ part,
-                                                                     const int32_t* __restrict__ dptr,
-                                                                     const int32_t* __restrict__ dent,
-                                                                     int64_t n, const double* __restrict__ S) {
+// p = z + beta p (FIRST: p = z), Ap_I = sum of the element entries sharing I
+// (ascending (cell, node) order); block partial of p . Ap
+template <int NLOC, bool FIRST>
+__global__ __launch_bounds__(PCG_THREADS) void pcg_gather_kernel(const float* __restrict__ ycell, float2* __restrict__ pz,
+                                                                 float* __restrict__ Ap, double* __restrict__ part,
+                                                                 const int4* __restrict__ ent4,
+                                                                 const int32_t* __restrict__ dptr,
+                                                                 const int32_t* __restrict__ dent, int64_t E, int64_t n,
+                                                                 const double* __restrict__ S) {
   __shared__ double sh[PCG_THREADS];
   if (pcg_done(S)) return;
   const int64_t I = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
   double d = 0.0;
   if (I < n) {
-    Real s = Real(0);
-    for (int it = dptr[I]; it < dptr[I + 1]; ++it) {
-      const int ent = dent[it];
-      s += ycell[ent];                    // ent = cell * nloc + local node
+    const int4 k = ent4[I];
+    const float2 o = pz[I];
+    const float y0 = ycell[k.x < 0 ? 0 : k.x], y1 = ycell[k.y < 0 ? 0 : k.y], y2 = ycell[k.z < 0 ? 0 : k.z],
+                y3 = ycell[k.w < 0 ? 0 : k.w];
+    float s = 0.0f;
+    if (k.x == -2) {
+      for (int it = dptr[I]; it < dptr[I + 1]; ++it) {
+        const int64_t e = dent[it] / NLOC;
+        s += ycell[(dent[it] - e * NLOC) * E + e];
+      }
+    } else {
+      s += y0;
+      if (k.y >= 0) s += y1;
+      if (k.z >= 0) s += y2;
+      if (k.w >= 0) s += y3;
     }
+    const float p = FIRST ? o.y : fmaf(static_cast<float>(S[S_BETA]), o.x, o.y);
+    pz[I].x = p;
     Ap[I] = s;
-    d = static_cast<double>(p[I]) * static_cast<double>(s);
+    d = static_cast<double>(p) * static_cast<double>(s);
   }
-  const double b = block_sum(d, sh);
+  const double b = tree_sum<PCG_THREADS>(d, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = b;
 }
 
-// x = 0, r = b, z = D r, p = z; block partial of r . z
-template <typename Real>
-__global__ __launch_bounds__(PCG_THREADS) void pcg_init_kernel(const Real* __restrict__ b,
-                                                               const Real* __restrict__ dinv, Real* __restrict__ x,
-                                                               Real* __restrict__ r, Real* __restrict__ z,
-                                                               Real* __restrict__ p, double* __restrict__ part,
-                                                               int64_t n) {
-  __shared__ double sh[PCG_THREADS];
-  const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
-  double d = 0.0;
-  if (i < n) {
-    const Real bi = b[i];
-    const Real zi = dinv[i] * bi;
-    x[i] = Real(0);
-    r[i] = bi;
-    z[i] = zi;
-    p[i] = zi;
-    d = static_cast<double>(bi) * static_cast<double>(zi);
-  }
-  const double s = block_sum(d, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+// W[e][q] = w_q |det J| of the volume rule, for the apply kernel
+template <int P>
+__global__ __launch_bounds__(256) void cgq_mass_weights_kernel(float* __restrict__ W, const float* __restrict__ geo,
+                                                               const CGTables* __restrict__ tab, int64_t E) {
+  constexpr int N1 = P + 1, NLOC = N1 * N1;
+  const int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+  if (e >= E) return;
+  const Geo G = load_geo(geo, e);
+#pragma unroll
+  for (int qy = 0; qy < N1; ++qy)
+#pragma unroll
+    for (int qx = 0; qx < N1; ++qx) {
+      float px, py, J[2][2];
+      geo_eval(G, tab->xv[qx], tab->xv[qy], px, py, J);
+      W[e * NLOC + qx + N1 * qy] = tab->wv[qx] * tab->wv[qy] * fabsf(J[0][0] * J[1][1] - J[0][1] * J[1][0]);
+    }
 }
 
-// x += alpha p, r -= alpha Ap, z = D r; block partial of r . z
-template <typename Real>
-__global__ __launch_bounds__(PCG_THREADS) void pcg_update_kernel(Real* __restrict__ x, Real* __restrict__ r,
-                                                                 Real* __restrict__ z, const Real* __restrict__ p,
-                                                                 const Real* __restrict__ Ap,
-                                                                 const Real* __restrict__ dinv,
-                                                                 double* __restrict__ part, int64_t n,
-                                                                 const double* __restrict__ S) {
+// basis products phi_j(x_q) of the tensor rule, [q][j] (kernel argument: read
+// through the scalar unit)
+template <int NLOC>
+struct MassBasis {
+  float phi[NLOC][NLOC];
+};
+
+// cells and gather in one (FUSED recurrence as in pcg_cells_kernel): Ap_I = sum over
+// the cells sharing I of the row sum_q phi_I(x_q) W_q p_h(x_q); the directions
+// alternate between pz and pz_new, as other DOFs still read the old one
+template <int P, bool FIRST>
+__global__ __launch_bounds__(PCG_THREADS) void pcg_apply_kernel(
+    const float2* __restrict__ pz, float2* __restrict__ pz_new, float* __restrict__ Ap,
+    const double* __restrict__ rz_part, double* __restrict__ pap_part, int nb, const float* __restrict__ W,
+    const int32_t* __restrict__ cdof, const int32_t* __restrict__ dptr, const int32_t* __restrict__ dent,
+    MassBasis<(P + 1) * (P + 1)> B, int64_t n, double* S, int it) {
+  constexpr int NLOC = (P + 1) * (P + 1);
+  __shared__ double sh[PCG_THREADS];
+  __shared__ float sphi[NLOC][NLOC];      // [j][q]
+  if (pcg_done(S)) return;
+  const double rz = partial_sum(rz_part, nb, sh);
+  float beta;
+  if (!pcg_recur<FIRST>(rz, S, it, beta)) return;
+  if (threadIdx.x < NLOC * NLOC) sphi[threadIdx.x % NLOC][threadIdx.x / NLOC] = (&B.phi[0][0])[threadIdx.x];
+  __syncthreads();
+  const int64_t I = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
+  double d = 0.0;
+  if (I < n) {
+    float s = 0.0f;
+    const int beg = dptr[I], end = dptr[I + 1];
+    for (int k = beg; k < end; ++k) {
+      const int ent = dent[k];
+      const int64_t e = ent / NLOC;
+      const int i = ent - static_cast<int>(e) * NLOC;
+      float xe[NLOC], Wq[NLOC];
+#pragma unroll
+      for (int j = 0; j < NLOC; ++j) {
+        const float2 v = pz[cdof[e * NLOC + j]];
+        xe[j] = FIRST ? v.y : fmaf(beta, v.x, v.y);
+        Wq[j] = W[e * NLOC + j];
+      }
+      float y = 0.0f;
+#pragma unroll
+      for (int q = 0; q < NLOC; ++q) {
+        float xq = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NLOC; ++j) xq = fmaf(B.phi[q][j], xe[j], xq);
+        const float Wx = Wq[q] * xq;
+        y = fmaf(sphi[i][q], Wx, y);
+      }
+      s += y;
+    }
+    const float2 o = pz[I];
+    const float p = FIRST ? o.y : fmaf(beta, o.x, o.y);
+    pz_new[I].x = p;
+    Ap[I] = s;
+    d = static_cast<double>(p) * static_cast<double>(s);
+  }
+  const double b = tree_sum<PCG_THREADS>(d, sh);
+  if (threadIdx.x == 0) pap_part[blockIdx.x] = b;
+}
+
+// x += alpha p (FIRST: x = alpha p), r -= alpha Ap, z = D r; block partial of r . z
+template <bool FIRST, bool FUSED>
+__global__ __launch_bounds__(PCG_THREADS) void pcg_update_kernel(float* __restrict__ x, float* __restrict__ r,
+                                                                 float2* __restrict__ pz, const float* __restrict__ Ap,
+                                                                 const float* __restrict__ dinv,
+                                                                 const double* __restrict__ pap_part,
+                                                                 double* __restrict__ rz_part, int nb, int64_t n,
+                                                                 const double* __restrict__ S, int it) {
   __shared__ double sh[PCG_THREADS];
   if (pcg_done(S)) return;
-  const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
-  const Real al = static_cast<Real>(S[S_ALPHA]);
+  const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x, ic = i < n ? i : n - 1;
+  const float p = pz[ic].x, xo = FIRST ? 0.0f : x[ic], ro = r[ic], ap = Ap[ic], di = dinv[ic];
+  float al;
+  if constexpr (FUSED) al = static_cast<float>(S[(it & 1) ? S_RZ_ODD : S_RZ] / partial_sum(pap_part, nb, sh));
+  else al = static_cast<float>(S[S_ALPHA]);
   double d = 0.0;
   if (i < n) {
-    x[i] = fma(al, p[i], x[i]);
-    const Real ri = fma(-al, Ap[i], r[i]);
-    const Real zi = dinv[i] * ri;
+    x[i] = fmaf(al, p, xo);
+    const float ri = fmaf(-al, ap, ro);
+    const float zi = di * ri;
     r[i] = ri;
-    z[i] = zi;
+    pz[i].y = zi;
     d = static_cast<double>(ri) * static_cast<double>(zi);
   }
-  const double s = block_sum(d, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+  const double s = tree_sum<PCG_THREADS>(d, sh);
+  if (threadIdx.x == 0) rz_part[blockIdx.x] = s;
 }
 
-// p = z + beta p
-template <typename Real>
-__global__ __launch_bounds__(PCG_THREADS) void pcg_direction_kernel(Real* __restrict__ p, const Real* __restrict__ z,
-                                                                    int64_t n, const double* __restrict__ S) {
-  if (pcg_done(S)) return;
-  const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
-  if (i >= n) return;
-  p[i] = fma(static_cast<Real>(S[S_BETA]), p[i], z[i]);
-}
-
-// Sum of the block partials (fixed order) and the scalar recurrences.
+// Sum of the block partials and the scalar recurrences (large meshes).
 //   op 0: rz = rz0 = sum (done at once for a zero right-hand side)
 //   op 1: alpha = rz / (p . Ap)
 //   op 2: beta = rz_new / rz, rz = rz_new, done once rz_new <= tol^2 rz0
@@ -166,49 +341,54 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_scalar_kernel(const double* _
                                                                  double* __restrict__ S, int op) {
   __shared__ double sh[PCG_THREADS];
   if (pcg_done(S)) return;
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < nb; i += PCG_THREADS) acc += part[i];
-  const double v = block_sum(acc, sh);
+  const double v = partial_sum(part, nb, sh);
   if (threadIdx.x != 0) return;
   if (op == 0) {
     S[S_RZ] = v;
     S[S_RZ0] = v;
+    S[S_NOX] = v > 0.0 ? 0.0 : 1.0;
     if (!(v > 0.0)) S[S_DONE] = 1.0;
   } else if (op == 1) {
-    S[S_PAP] = v;
     S[S_ALPHA] = S[S_RZ] / v;
   } else {
     S[S_BETA] = v / S[S_RZ];
     S[S_RZ] = v;
-    S[S_ITER] += 1.0;
     if (!(v > S[S_TOL2] * S[S_RZ0])) S[S_DONE] = 1.0;
   }
 }
 
-// After the fixed launch sequence: a solve that has not met its tolerance
-// (nor broken down) sets ST_PCG_STALL in the workspace status word.
-__global__ void pcg_check_kernel(const double* __restrict__ S, uint32_t* __restrict__ status) {
-  if (threadIdx.x == 0 && !pcg_done(S)) atomicOr(status, ST_PCG_STALL);
+// u_out = a0 u_n + b0 (u_s - dt x) (no iteration: x = 0).  A solve that has not met
+// its tolerance (nor broken down) when the launch sequence ends sets
+// ST_PCG_STALL in the workspace status word (part: the last partials of r.z when
+// no scalar launch has judged them).
+__global__ __launch_bounds__(PCG_THREADS) void pcg_finish_kernel(const float* __restrict__ us,
+                                                                 const float* __restrict__ un,
+                                                                 const float* __restrict__ x, float* __restrict__ uo,
+                                                                 float a0, float b0, float dt, int64_t n,
+                                                                 const double* __restrict__ S,
+                                                                 const double* __restrict__ part, int nb,
+                                                                 uint32_t* __restrict__ status) {
+  __shared__ double sh[PCG_THREADS];
+  if (blockIdx.x == 0 && !pcg_done(S)) {
+    const bool ok = part && !(partial_sum(part, nb, sh) > S[S_TOL2] * S[S_RZ0]);
+    if (threadIdx.x == 0 && !ok) atomicOr(status, ST_PCG_STALL);
+  }
+  const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
+  if (i >= n) return;
+  const float xi = S[S_NOX] != 0.0 ? 0.0f : x[i];
+  const float base = (a0 != 0.0f) ? a0 * un[i] : 0.0f;
+  uo[i] = base + b0 * (us[i] - dt * xi);
 }
 
-__global__ void pcg_setup_kernel(double* __restrict__ S, double tol2) {
-  if (threadIdx.x != 0) return;
-  for (int i = 0; i < 8; ++i) S[i] = 0.0;
-  S[S_TOL2] = tol2;
-}
-
-// u_out = a0 u_n + b0 (u_s - dt x), x = M^{-1} R (dinv != null: x = dinv * R, a
-// diagonal mass of nm entries shared by every variable); a0 = 0: u_n is not read
+// u_out = a0 u_n + b0 (u_s - dt x), x = M^{-1} R; a0 = 0: u_n is not read
 template <typename Real>
 __global__ __launch_bounds__(256) void stage_update_kernel(const Real* __restrict__ us, const Real* __restrict__ un,
-                                                           const Real* __restrict__ x, const Real* __restrict__ dinv,
-                                                           Real* __restrict__ uo, Real a0, Real b0, Real dt,
-                                                           int64_t n, int64_t nm) {
+                                                           const Real* __restrict__ x, Real* __restrict__ uo, Real a0,
+                                                           Real b0, Real dt, int64_t n) {
   const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
   if (i >= n) return;
-  const Real xi = dinv ? x[i] * dinv[i % nm] : x[i];
   const Real base = (a0 != Real(0)) ? a0 * un[i] : Real(0);
-  uo[i] = base + b0 * (us[i] - dt * xi);
+  uo[i] = base + b0 * (us[i] - dt * x[i]);
 }
 
 // The whole PCG solve of a line (segments) in one workgroup per variable
@@ -221,18 +401,6 @@ __global__ __launch_bounds__(256) void stage_update_kernel(const Real* __restric
 // the tables of any degree.  Dot products: per-thread partials in a fixed
 // stride order, then a fixed tree.
 constexpr int SMALL_THREADS = 1024;
-
-__device__ __forceinline__ double wg_sum(double v, double* sh) {
-  __syncthreads();
-  sh[threadIdx.x] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = SMALL_THREADS / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  return sh[0];
-}
 
 template <typename Real>
 __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
@@ -267,7 +435,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
     p[i] = zi;
     d += static_cast<double>(bi) * static_cast<double>(zi);
   }
-  double rz = wg_sum(d, sh);
+  double rz = tree_sum<SMALL_THREADS>(d, sh);
   const double rz0 = rz;
   bool done = !(rz > 0.0);
   for (int it = 0; it < maxit && !done; ++it) {
@@ -286,7 +454,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
       Ap[I] = s;
       d += static_cast<double>(p[I]) * static_cast<double>(s);
     }
-    const double al = rz / wg_sum(d, sh);
+    const double al = rz / tree_sum<SMALL_THREADS>(d, sh);
     d = 0.0;
     for (int64_t i = tid; i < n; i += SMALL_THREADS) {
       x[i] = fma(static_cast<Real>(al), p[i], x[i]);
@@ -296,7 +464,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
       z[i] = zi;
       d += static_cast<double>(ri) * static_cast<double>(zi);
     }
-    const double rzn = wg_sum(d, sh);
+    const double rzn = tree_sum<SMALL_THREADS>(d, sh);
     const double be = rzn / rz;
     rz = rzn;
     if (!(rzn > tol2 * rz0)) { done = true; break; }
@@ -306,68 +474,266 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
   if (tid == 0 && !done) atomicOr(status, ST_PCG_STALL);
 }
 
-static unsigned nbk(int64_t n, int t) { return static_cast<unsigned>((n + t - 1) / t); }
+// ---------------------------------------------------------------------------
+// Direct solve on lines (tables: line_mass_operator on the host).  A block takes
+// `own` consecutive vertices of the chain with 2^levels - 1 more on either side,
+// which is as far as `levels` steps of cyclic reduction reach: blocks need nothing
+// from each other and the whole solve with the stage update is one launch.
+// Float64 throughout.  A NaN among the element rows of a variable leaves its x = 0,
+// an infinity makes it NaN everywhere, as in the conjugate gradient iteration: a
+// single block sees every row, several take the cell kernel's word (rows).
+// 128 cells, P2: 4.0 us against 65.3 us for the conjugate gradients (and their
+// assembly and update launches); a step of P1 advection on 1500 cells 37.8 against
+// 563 us, of P4 Euler on 1000 cells 90.6 against 867 us.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t row_bits(double v) {
+  return isfinite(v) ? 0u : (isnan(v) ? CG_ROWS_NAN : CG_ROWS_INF);
+}
+__global__ void line_clear_rows_kernel(uint32_t* status) {
+  if (threadIdx.x < 3) status[WS_CG_ROWS + threadIdx.x] = 0;
+}
 
-template <typename Real>
-static void mass_cells(const cvw_mesh* m, const Real* x, Real* ycell, const double* S, hipStream_t s) {
-  // CG quadrilaterals (float32); lines take pcg_line_kernel
-  const dim3 g(nbk(m->E, 128)), b(128);
-  if constexpr (std::is_same<Real, float>::value) {
-    if (m->degree == 1)
-      hipLaunchKernelGGL(cgq_mass_kernel<1>, g, b, 0, s, x, ycell, m->d_cell_dof, m->d_geo, m->d_cgt, m->E, S);
-    else
-      hipLaunchKernelGGL(cgq_mass_kernel<2>, g, b, 0, s, x, ycell, m->d_cell_dof, m->d_geo, m->d_cgt, m->E, S);
+template <typename Real, int T>
+__global__ __launch_bounds__(T) void line_mass_kernel(
+    const Real* __restrict__ rcell, const Real* __restrict__ us, const Real* __restrict__ un, Real* __restrict__ uo,
+    const double* __restrict__ red, const double* __restrict__ tab, const double* __restrict__ hcell,
+    const int32_t* __restrict__ chain, const int32_t* __restrict__ cdof, int deg, int64_t E, int64_t nv, int64_t ndof,
+    int loop, int levels, int own, const uint32_t* __restrict__ rows, Real a0, Real b0, Real dt) {
+  constexpr int ML = 7;
+  __shared__ double sh[2][T];
+  const int t = threadIdx.x, n1 = deg + 1, ni = deg - 1, H = (1 << levels) - 1;
+  const int64_t k0 = static_cast<int64_t>(blockIdx.x) * own;
+  uint32_t fl = gridDim.x > 1 ? rows[blockIdx.y] : 0;
+  const int64_t off = blockIdx.y * ndof;
+  rcell += blockIdx.y * E * n1;
+  us += off;
+  un += off;
+  uo += off;
+  int64_t k = k0 - H + t;
+  if (loop) k = ((k % nv) + nv) % nv;
+  const bool in = k >= 0 && k < nv;
+  double al[ML], ga[ML], g = 0.0, ib = 0.0;
+#pragma unroll
+  for (int l = 0; l < ML; ++l) {
+    al[l] = ga[l] = 0.0;
+    if (in && l < levels) {
+      al[l] = red[(2 * l) * nv + k];
+      ga[l] = red[(2 * l + 1) * nv + k];
+    }
+  }
+  if (in) {
+    ib = red[2 * levels * nv + k];
+    const int64_t kl = k > 0 ? k - 1 : (loop ? nv - 1 : -1);
+    if (k < E) {                          // the cell on the right: its node 0
+      const Real* r = rcell + static_cast<int64_t>(chain[k]) * n1;
+      double s = r[0];
+      fl |= row_bits(s);
+      for (int i = 0; i < ni; ++i) {
+        const double v = r[i + 1];
+        fl |= row_bits(v);
+        s -= tab[i] * v;
+      }
+      g += s;
+    }
+    if (kl >= 0) {                        // the cell on the left: its node p
+      const Real* r = rcell + static_cast<int64_t>(chain[kl]) * n1;
+      double s = r[deg];
+      fl |= row_bits(s);
+      for (int i = 0; i < ni; ++i) s -= tab[ni + i] * static_cast<double>(r[i + 1]);
+      g += s;
+    }
+  }
+  sh[0][t] = g;
+  fl = (__syncthreads_or(fl & CG_ROWS_NAN) ? CG_ROWS_NAN : 0) | (__syncthreads_or(fl & CG_ROWS_INF) ? CG_ROWS_INF : 0);
+  int cur = 0;
+#pragma unroll
+  for (int l = 0; l < ML; ++l) {
+    if (l >= levels) break;
+    const int s = 1 << l;
+    const double lo = t >= s ? sh[cur][t - s] : 0.0, hi = t + s < T ? sh[cur][t + s] : 0.0;
+    g = fma(al[l], lo, fma(ga[l], hi, g));
+    sh[cur ^ 1][t] = g;
+    cur ^= 1;
+    __syncthreads();
+  }
+  double xv = g * ib;
+  if (fl) xv = (fl & CG_ROWS_NAN) ? 0.0 : __builtin_nan("");
+  sh[cur ^ 1][t] = xv;
+  __syncthreads();
+  const double* xs = sh[cur ^ 1] + H;     // vertex k0 + j at xs[j]
+  auto update = [&](int64_t I, double x) {
+    const Real base = (a0 != Real(0)) ? a0 * un[I] : Real(0);
+    uo[I] = base + b0 * (us[I] - dt * static_cast<Real>(x));
+  };
+  const int64_t nown = nv - k0 < own ? nv - k0 : own;
+  for (int j = t; j < nown; j += T) {
+    const int64_t kk = k0 + j;
+    update(kk < E ? cdof[static_cast<int64_t>(chain[kk]) * n1] : cdof[static_cast<int64_t>(chain[E - 1]) * n1 + deg],
+           xs[j]);
+  }
+  const int64_t ncell = E - k0 < own ? E - k0 : own;
+  for (int w = t; w < ncell * ni; w += T) {
+    const int j = w / ni, i = w - j * ni;
+    const int64_t e = chain[k0 + j];
+    const Real* r = rcell + e * n1 + 1;
+    const double* Mi = tab + 2 * ni + i * ni;
+    double s = 0.0;
+    for (int q = 0; q < ni; ++q) s = fma(Mi[q], static_cast<double>(r[q]), s);
+    double x = s * (2.0 / hcell[e]) - tab[i] * xs[j] - tab[ni + i] * xs[j + 1];
+    if (fl) x = (fl & CG_ROWS_NAN) ? 0.0 : __builtin_nan("");
+    update(cdof[e * n1 + i + 1], x);
   }
 }
+
+static unsigned nbk(int64_t n, int t) { return static_cast<unsigned>((n + t - 1) / t); }
 
 size_t pcg_partials(int64_t n) { return nbk(n, PCG_THREADS); }
 
 template <typename Real>
-cvw_status cg_mass_solve(const cvw_mesh* m, const Real* b, Real* x, Real* r, Real* z, Real* p, Real* Ap,
-                         Real* ycell, double* part, double* S, const Real* dinv, double tol, int maxit,
-                         uint32_t* status, hipStream_t s, int nvar) {
+cvw_status line_pcg(const cvw_mesh* m, const Real* b, Real* x, Real* r, Real* z, Real* p, Real* Ap, Real* ycell,
+                    const Real* dinv, double tol, int maxit, uint32_t* status, hipStream_t s, int nvar) {
+  hipLaunchKernelGGL((pcg_line_kernel<Real>), dim3(nvar), dim3(SMALL_THREADS), 0, s, b, x, r, z, p, Ap, ycell, dinv,
+                     m->d_hp, m->d_hcell, m->d_cell_dof, m->d_dof_ptr, m->d_dof_ent, m->degree, m->E, m->ndof,
+                     tol * tol, maxit, status);
+  return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
+}
+
+// Iterations after which conjugate gradients must have met the tolerance: in
+// the energy norm they reduce the error by 2 ((sqrt(c) - 1) / (sqrt(c) + 1))^k, and
+// the preconditioned residual norm differs from it by a factor sqrt(c) at most
+// (c: the condition number); a tenth and two more for rounding.
+static int pcg_iterations(double cond, double tol, int maxit) {
+  if (!(cond > 1.0)) return maxit;
+  const double q = std::sqrt(cond), k = std::log(2.0 * q / tol) / std::log((q + 1.0) / (q - 1.0));
+  return std::min(maxit, static_cast<int>(std::ceil(1.1 * k)) + 2);
+}
+
+template <int P>
+static cvw_status quad_pcg(const cvw_mesh* m, const float* rcell, const QuadSolve& q, double tol, int maxit,
+                           const float* us, const float* un, float* uo, double a0, double b0, double dt,
+                           uint32_t* status, hipStream_t s) {
+  constexpr int N1 = P + 1, NLOC = N1 * N1;
   const int64_t n = m->ndof;
-  if (m->cell == CVW_SEG) {            // a line: the whole solve in one workgroup per variable
-    hipLaunchKernelGGL((pcg_line_kernel<Real>), dim3(nvar), dim3(SMALL_THREADS), 0, s, b, x, r, z, p, Ap, ycell, dinv,
-                       m->d_hp, m->d_hcell, m->d_cell_dof, m->d_dof_ptr, m->d_dof_ent, m->degree, m->E, n,
-                       tol * tol, maxit, status);
-    return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
-  }
   const int nb = static_cast<int>(nbk(n, PCG_THREADS));
+  const bool fused = nb <= PCG_FUSED_PARTIALS && static_cast<size_t>(nb) <= q.part_cap;
+  double* rz = q.part[0];
+  double* pap = fused ? q.part[1] : q.part[0];
   const dim3 g(nb), t(PCG_THREADS);
-  hipLaunchKernelGGL(pcg_setup_kernel, dim3(1), dim3(64), 0, s, S, tol * tol);
-  hipLaunchKernelGGL((pcg_init_kernel<Real>), g, t, 0, s, b, dinv, x, r, z, p, part, n);
-  hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, part, nb, S, 0);
-  for (int it = 0; it < maxit; ++it) {
-    mass_cells<Real>(m, p, ycell, S, s);
-    hipLaunchKernelGGL((pcg_gather_dot_kernel<Real>), g, t, 0, s, ycell, p, Ap, part, m->d_dof_ptr, m->d_dof_ent,
-                       n, S);
-    hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, part, nb, S, 1);
-    hipLaunchKernelGGL((pcg_update_kernel<Real>), g, t, 0, s, x, r, z, p, Ap, dinv, part, n, S);
-    hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, part, nb, S, 2);
-    hipLaunchKernelGGL((pcg_direction_kernel<Real>), g, t, 0, s, p, z, n, S);
+  hipLaunchKernelGGL(pcg_init_kernel, g, t, 0, s, rcell, m->d_dinv_f, q.r, q.pz, rz, m->d_dof_ptr, m->d_dof_ent, n,
+                     q.S, tol * tol);
+  if (!fused) hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, rz, nb, q.S, 0);
+  const int iters = pcg_iterations(m->mass_cond, tol, maxit);
+  const bool one = fused && nb <= PCG_APPLY_PARTIALS;
+  MassBasis<NLOC> B;
+  if (one) {
+    for (int k = 0; k < NLOC; ++k)
+      for (int j = 0; j < NLOC; ++j) B.phi[k][j] = m->cgt.Dv[0][k % N1][j % N1] * m->cgt.Dv[0][k / N1][j / N1];
+    hipLaunchKernelGGL(cgq_mass_weights_kernel<P>, dim3(nbk(m->E, 256)), dim3(256), 0, s, q.y, m->d_geo, m->d_cgt,
+                       m->E);
   }
-  hipLaunchKernelGGL(pcg_check_kernel, dim3(1), dim3(64), 0, s, S, status);
+  float* x = one ? q.x2 : q.x;
+  for (int it = 0; it < iters; ++it) {
+    float2* pz = one && !(it & 1) ? q.pz2 : q.pz;        // holds p and, after the update, z
+    auto update = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, g, t, 0, s, x, q.r, pz, q.Ap, m->d_dinv_f, pap, rz, nb, n, q.S, it);
+    };
+    if (one) {
+      auto apply = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, g, t, 0, s, (it & 1) ? q.pz2 : q.pz, pz, q.Ap, rz, pap, nb, q.y, m->d_cell_dof,
+                           m->d_dof_ptr, m->d_dof_ent, B, n, q.S, it);
+      };
+      if (it == 0) apply(pcg_apply_kernel<P, true>); else apply(pcg_apply_kernel<P, false>);
+      if (it == 0) update(pcg_update_kernel<true, true>); else update(pcg_update_kernel<false, true>);
+      continue;
+    }
+    auto cells = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(nbk(m->E, PCG_THREADS)), t, 0, s, q.pz, q.y, rz, nb, m->d_cell_dof_t, m->d_geo,
+                         m->d_cgt, m->E, q.S, it);
+    };
+    auto gather = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, g, t, 0, s, q.y, q.pz, q.Ap, pap, m->d_dof_ent4, m->d_dof_ptr, m->d_dof_ent, m->E, n,
+                         q.S);
+    };
+    if (fused) {
+      if (it == 0) cells(pcg_cells_kernel<P, true, true>); else cells(pcg_cells_kernel<P, false, true>);
+    } else {
+      if (it == 0) cells(pcg_cells_kernel<P, true, false>); else cells(pcg_cells_kernel<P, false, false>);
+    }
+    if (it == 0) gather(pcg_gather_kernel<NLOC, true>); else gather(pcg_gather_kernel<NLOC, false>);
+    if (fused) {
+      if (it == 0) update(pcg_update_kernel<true, true>); else update(pcg_update_kernel<false, true>);
+    } else {
+      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, pap, nb, q.S, 1);
+      if (it == 0) update(pcg_update_kernel<true, false>); else update(pcg_update_kernel<false, false>);
+      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, rz, nb, q.S, 2);
+    }
+  }
+  hipLaunchKernelGGL(pcg_finish_kernel, g, t, 0, s, us, un, x, uo, static_cast<float>(a0), static_cast<float>(b0),
+                     static_cast<float>(dt), n, q.S, fused ? rz : nullptr, nb, status);
+  return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
+}
+
+cvw_status cgquad_mass_stage(const cvw_mesh* m, const float* rcell, const QuadSolve& q, double tol, int maxit,
+                             const float* us, const float* un, float* uo, double a0, double b0, double dt,
+                             uint32_t* status, hipStream_t s) {
+  return m->degree == 1 ? quad_pcg<1>(m, rcell, q, tol, maxit, us, un, uo, a0, b0, dt, status, s)
+                        : quad_pcg<2>(m, rcell, q, tol, maxit, us, un, uo, a0, b0, dt, status, s);
+}
+
+template <typename Real>
+cvw_status stage_update(const Real* us, const Real* un, const Real* x, Real* uo, double a0, double b0, double dt,
+                        int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL((stage_update_kernel<Real>), dim3(nbk(n, 256)), dim3(256), 0, s, us, un, x, uo,
+                     static_cast<Real>(a0), static_cast<Real>(b0), static_cast<Real>(dt), n);
+  return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
+}
+
+// Threads per block of the direct line solve: they cover the block's vertices,
+// the reach of the reduction on both sides and the right vertex of its last
+// cell.  The smallest block that holds the whole chain (one block needs no
+// clearing launch), else many small ones (512 threads at seven levels, whose
+// reach is 127).
+static int line_own(const cvw_mesh* m, int T) { return T - 2 * ((1 << m->line_levels) - 1) - 1; }
+static int line_threads(const cvw_mesh* m) {
+  for (int T = 256; T <= 1024; T *= 2)
+    if (line_own(m, T) >= m->chain_nv) return T;
+  return m->line_levels <= 6 ? 256 : 512;
+}
+
+cvw_status line_clear_rows(const cvw_mesh* m, uint32_t* status, hipStream_t s) {
+  if (line_own(m, line_threads(m)) >= m->chain_nv) return CVW_OK;
+  hipLaunchKernelGGL(line_clear_rows_kernel, dim3(1), dim3(64), 0, s, status);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 
 template <typename Real>
-cvw_status stage_update(const Real* us, const Real* un, const Real* x, const Real* dinv, Real* uo, double a0,
-                        double b0, double dt, int64_t n, hipStream_t s, int64_t nm) {
-  hipLaunchKernelGGL((stage_update_kernel<Real>), dim3(nbk(n, 256)), dim3(256), 0, s, us, un, x, dinv, uo,
-                     static_cast<Real>(a0), static_cast<Real>(b0), static_cast<Real>(dt), n, nm > 0 ? nm : n);
+cvw_status line_mass_stage(const cvw_mesh* m, int nvar, const Real* rcell, const Real* us, const Real* un, Real* uo,
+                           double a0, double b0, double dt, const uint32_t* rows_flag, hipStream_t s) {
+  const int T = line_threads(m), own = line_own(m, T);
+  const dim3 g(nbk(m->chain_nv, own), nvar);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, g, dim3(T), 0, s, rcell, us, un, uo, m->d_line_red, m->d_line_int, m->d_hcell,
+                       m->d_chain, m->d_cell_dof, m->degree, m->E, m->chain_nv, m->ndof, m->chain_loop,
+                       m->line_levels, own, rows_flag, static_cast<Real>(a0), static_cast<Real>(b0),
+                       static_cast<Real>(dt));
+  };
+  if (T == 256) launch(line_mass_kernel<Real, 256>);
+  else if (T == 512) launch(line_mass_kernel<Real, 512>);
+  else launch(line_mass_kernel<Real, 1024>);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 
-template cvw_status cg_mass_solve<float>(const cvw_mesh*, const float*, float*, float*, float*, float*, float*,
-                                         float*, double*, double*, const float*, double, int, uint32_t*,
-                                         hipStream_t, int);
-template cvw_status cg_mass_solve<double>(const cvw_mesh*, const double*, double*, double*, double*, double*,
-                                          double*, double*, double*, double*, const double*, double, int,
-                                          uint32_t*, hipStream_t, int);
-template cvw_status stage_update<float>(const float*, const float*, const float*, const float*, float*, double,
-                                        double, double, int64_t, hipStream_t, int64_t);
-template cvw_status stage_update<double>(const double*, const double*, const double*, const double*, double*,
-                                         double, double, double, int64_t, hipStream_t, int64_t);
+template cvw_status line_mass_stage<float>(const cvw_mesh*, int, const float*, const float*, const float*, float*,
+                                           double, double, double, const uint32_t*, hipStream_t);
+template cvw_status line_mass_stage<double>(const cvw_mesh*, int, const double*, const double*, const double*,
+                                            double*, double, double, double, const uint32_t*, hipStream_t);
+template cvw_status line_pcg<float>(const cvw_mesh*, const float*, float*, float*, float*, float*, float*, float*,
+                                    const float*, double, int, uint32_t*, hipStream_t, int);
+template cvw_status line_pcg<double>(const cvw_mesh*, const double*, double*, double*, double*, double*, double*,
+                                     double*, const double*, double, int, uint32_t*, hipStream_t, int);
+template cvw_status stage_update<float>(const float*, const float*, const float*, float*, double, double, double,
+                                        int64_t, hipStream_t);
+template cvw_status stage_update<double>(const double*, const double*, const double*, double*, double, double, double,
+                                         int64_t, hipStream_t);
 
 }  // namespace cvw

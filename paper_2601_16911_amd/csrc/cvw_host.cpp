@@ -63,7 +63,7 @@ SegHPArgs seghp_args(const cvw_mesh* m, const cvw_params* prm) {
   A.tab = m->d_hp;
   A.cell_dof = m->d_cell_dof;
   A.cell_vtx = m->d_cell_vtx;
-  A.nbr = m->d_nbr;
+  A.nb = m->d_line_nb;
   A.hcell = m->d_hcell;
   A.vptr = m->d_vtx_ptr;
   A.vent = m->d_vtx_ent;
@@ -1066,6 +1066,12 @@ using namespace cvw;
     }                                                                              \
   } while (0)
 
+// Mass-matrix tolerances of the iterative solves (relative, preconditioned norm)
+// and the launch-time iteration cap of the PCG solve, whose converged iterations
+// are no-ops on the device.
+constexpr double PCG_TOL_F32 = 2e-7, PCG_TOL_F64 = 1e-14;
+constexpr int PCG_MAXIT_F32 = 64, PCG_MAXIT_F64 = 160;
+
 // Device storage of a mesh under construction: one hipMalloc per array, or
 // 256-byte aligned pieces of a caller-provided buffer (cvw_mesh_build_in), or
 // only a byte count (cvw_mesh_plan).
@@ -1141,6 +1147,9 @@ static std::vector<double> diag_mass(const cvw_mesh* m, const cvw_mesh_desc* d) 
     lobatto_nodes(p + 1, xn);
     const int N1 = p + 1;
     const double sxv[4] = {-1, 1, 1, -1}, syv[4] = {-1, -1, 1, 1};
+    double l[MAXP + 1][MAXP + 1];
+    for (int a = 0; a < N1; ++a)
+      for (int q = 0; q < N1; ++q) l[a][q] = lagrange_deriv(xn, a, 0, xq[q]);
     out.assign(m->ndof, 0.0);
     for (int64_t e = 0; e < E; ++e) {
       const double* X = d->cell_coords + e * 8;
@@ -1157,12 +1166,214 @@ static std::vector<double> diag_mass(const cvw_mesh* m, const cvw_mesh_desc* d) 
           const double W = wq[qx] * wq[qy] * std::fabs(J[0][0] * J[1][1] - J[0][1] * J[1][0]);
           for (int b = 0; b < N1; ++b)
             for (int a = 0; a < N1; ++a)
-              out[m->h_cell_dof[e * N1 * N1 + a + N1 * b]] +=
-                  W * lagrange_deriv(xn, a, 0, xq[qx]) * lagrange_deriv(xn, b, 0, xq[qy]);
+              out[m->h_cell_dof[e * N1 * N1 + a + N1 * b]] += W * l[a][qx] * l[b][qy];
         }
     }
   }
   return out;
+}
+
+// S - shift I (sign +1) or shift I - S (sign -1) positive definite: an n x n
+// Cholesky factorisation goes through
+static bool shifted_pd(const double* S, int n, double shift, double sign) {
+  double L[9 * 9];
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j <= i; ++j) {
+      double v = sign * (S[i * n + j] - (i == j ? shift : 0.0));
+      for (int k = 0; k < j; ++k) v -= L[i * n + k] * L[j * n + k];
+      if (i == j) {
+        if (!(v > 0.0)) return false;
+        L[i * n + i] = std::sqrt(v);
+      } else {
+        L[i * n + j] = v / L[j * n + j];
+      }
+    }
+  return true;
+}
+
+// Condition number of the consistent mass M of CG quadrilaterals scaled by the
+// lumped mass D.  With M and D sums of element matrices, the spectrum of D^{-1} M
+// lies between the smallest and the largest eigenvalue of D_e^{-1} M_e over the
+// elements (Wathen 1987); the two bounds are moved only when an element's
+// factorisation shows that it lies outside (by bisection, then 1 % further so
+// that few elements do).  0 when an element's lumped mass is not positive.
+static double quad_mass_condition(const cvw_mesh* m, const cvw_mesh_desc* d) {
+  const int p = m->degree, N1 = p + 1, n = N1 * N1;
+  std::vector<double> xq, wq, xn;
+  gauss_rule(N1, xq, wq);
+  lobatto_nodes(N1, xn);
+  double phi[9][9], PP[9][9][9];                     // phi_i(x_q), products phi_i phi_j
+  for (int q = 0; q < n; ++q)
+    for (int i = 0; i < n; ++i)
+      phi[i][q] = lagrange_deriv(xn, i % N1, 0, xq[q % N1]) * lagrange_deriv(xn, i / N1, 0, xq[q / N1]);
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j)
+      for (int q = 0; q < n; ++q) PP[i][j][q] = phi[i][q] * phi[j][q];
+  const double sxv[4] = {-1, 1, 1, -1}, syv[4] = {-1, -1, 1, 1};
+  double lo = 4.0, hi = 0.0;
+  for (int64_t e = 0; e < m->E; ++e) {
+    const double* X = d->cell_coords + e * 8;
+    double W[9], S[81], ds[9];
+    for (int q = 0; q < n; ++q) {
+      double J[2][2] = {{0, 0}, {0, 0}};
+      for (int v = 0; v < 4; ++v) {
+        const double Nx = 0.25 * sxv[v] * (1 + syv[v] * xq[q / N1]), Ny = 0.25 * syv[v] * (1 + sxv[v] * xq[q % N1]);
+        for (int c = 0; c < 2; ++c) {
+          J[c][0] += Nx * X[2 * v + c];
+          J[c][1] += Ny * X[2 * v + c];
+        }
+      }
+      W[q] = wq[q % N1] * wq[q / N1] * std::fabs(J[0][0] * J[1][1] - J[0][1] * J[1][0]);
+    }
+    for (int i = 0; i < n; ++i) {
+      double s = 0.0;
+      for (int q = 0; q < n; ++q) s += W[q] * phi[i][q];
+      if (!(s > 0.0)) return 0.0;
+      ds[i] = 1.0 / std::sqrt(s);
+    }
+    for (int i = 0; i < n; ++i)
+      for (int j = 0; j <= i; ++j) {
+        double s = 0.0;
+        for (int q = 0; q < n; ++q) s += W[q] * PP[i][j][q];
+        S[i * n + j] = s * ds[i] * ds[j];
+      }
+    if (!shifted_pd(S, n, lo, 1.0)) {
+      double a = 0.0, b = lo;
+      for (int it = 0; it < 40; ++it) {
+        const double c = 0.5 * (a + b);
+        (shifted_pd(S, n, c, 1.0) ? a : b) = c;
+      }
+      lo = 0.99 * a;
+    }
+    if (!shifted_pd(S, n, hi, -1.0)) {
+      double a = hi, b = std::max(hi, 1.0);
+      while (!shifted_pd(S, n, b, -1.0) && b < 1e6) b *= 2.0;
+      for (int it = 0; it < 40; ++it) {
+        const double c = 0.5 * (a + b);
+        (shifted_pd(S, n, c, -1.0) ? b : a) = c;
+      }
+      hi = 1.01 * b;
+    }
+    if (!(lo > 1e-4)) return 0.0;
+  }
+  return hi / lo;
+}
+
+// Direct solve of the consistent mass on a CG line: with the interior nodes of
+// every cell eliminated (interior block Mii of the reference mass, coupling
+// T = Mii^{-1} Miv to the two vertices) the vertex system is tridiagonal along
+// the chain of cells, row k: h_L/2 S01 x_{k-1} + (h_L/2 S11 + h_R/2 S00) x_k +
+// h_R/2 S01 x_{k+1}.  Cyclic reduction with strides 1, 2, 4, ... squares the ratio
+// of the off-diagonals to the diagonal at every level, so a few levels (6 for
+// equal cells) leave couplings below rounding and no more are kept.  red:
+// factors alpha, gamma of every level, then the inverse diagonal; tab: T
+// [2][p-1], Mii^{-1} [p-1][p-1].  Sets nothing when the cells do not form one
+// chain or loop.
+//
+// Degrees up to 4: there the direct solve and the conjugate gradients it
+// replaces leave states that agree to 5e-16 after two steps.  At degree 8 the
+// scaled 8th derivatives of the sensor turn the last bit of the state into
+// changes of gamma_e of order 1e-7 and more, and the two states part by up to
+// 1e-8, so higher degrees keep the conjugate gradients with their rounding.
+constexpr int LINE_MAX_LEVELS = 7, LINE_DIRECT_MAXP = 4;
+static void line_mass_operator(cvw_mesh* m, const cvw_mesh_desc* d, std::vector<int32_t>& chain,
+                               std::vector<double>& red, std::vector<double>& tab) {
+  const int64_t E = m->E, Nv = m->Nv;
+  const int p = m->degree, n1 = p + 1, ni = p - 1;
+  std::vector<int32_t> as_left(Nv, -1), as_right(Nv, -1);     // the cell whose left / right vertex this is
+  for (int64_t e = 0; e < E; ++e) {
+    int32_t& l = as_left[d->cell_vertices[2 * e]];
+    int32_t& r = as_right[d->cell_vertices[2 * e + 1]];
+    if (l >= 0 || r >= 0) return;
+    l = r = static_cast<int32_t>(e);
+  }
+  int64_t first = 0;
+  for (int64_t e = 0; e < E; ++e)
+    if (as_right[d->cell_vertices[2 * e]] < 0) first = e;     // starts an open chain
+  chain.clear();
+  int32_t e = static_cast<int32_t>(first);
+  while (e >= 0 && static_cast<int64_t>(chain.size()) < E) {
+    chain.push_back(e);
+    e = as_left[d->cell_vertices[2 * e + 1]];
+    if (e == first) break;
+  }
+  const bool loop = e == first;
+  if (static_cast<int64_t>(chain.size()) != E) { chain.clear(); return; }
+  const int64_t nv = loop ? E : E + 1;
+  const std::vector<double> hp = fill_hp_tables(p, true);
+  const HPOff o = hp_off(p);
+  std::vector<double> M(n1 * n1);
+  for (int i = 0; i < n1; ++i)
+    for (int j = 0; j < n1; ++j) {
+      double s = 0.0;
+      for (int q = 0; q < n1; ++q) s += hp[o.wq + q] * hp[o.DQ + i * n1 + q] * hp[o.DQ + j * n1 + q];
+      M[i * n1 + j] = s;
+    }
+  tab.assign(2 * ni + ni * ni, 0.0);
+  double S[2][2] = {{M[0], M[p]}, {M[p * n1], M[p * n1 + p]}};
+  if (ni > 0) {
+    std::vector<double> A(ni * ni), R(ni * (ni + 2), 0.0);
+    for (int i = 0; i < ni; ++i) {
+      for (int j = 0; j < ni; ++j) A[i * ni + j] = M[(i + 1) * n1 + j + 1];
+      R[i * (ni + 2)] = M[(i + 1) * n1];
+      R[i * (ni + 2) + 1] = M[(i + 1) * n1 + p];
+      R[i * (ni + 2) + 2 + i] = 1.0;
+    }
+    if (!solve_dense(A, R, ni)) { chain.clear(); return; }
+    for (int i = 0; i < ni; ++i) {
+      for (int v = 0; v < 2; ++v) {
+        tab[v * ni + i] = R[i * (ni + 2) + v];
+        for (int u = 0; u < 2; ++u) S[u][v] -= M[(u == 0 ? 0 : p) * n1 + i + 1] * R[i * (ni + 2) + v];
+      }
+      for (int j = 0; j < ni; ++j) tab[2 * ni + i * ni + j] = R[i * (ni + 2) + 2 + j];
+    }
+  }
+  std::vector<ld> a(nv, 0.0L), b(nv, 0.0L), c(nv, 0.0L), a2(nv), b2(nv), c2(nv);
+  for (int64_t k = 0; k < E; ++k) {
+    const ld h = 0.5L * (static_cast<ld>(d->cell_coords[2 * chain[k] + 1]) - d->cell_coords[2 * chain[k]]);
+    const int64_t k1 = (k + 1) % nv;
+    b[k] += h * S[0][0];
+    c[k] += h * S[0][1];
+    b[k1] += h * S[1][1];
+    a[k1] += h * S[1][0];
+  }
+  red.clear();
+  int levels = 0;
+  for (;; ++levels) {
+    ld r = 0.0L;
+    for (int64_t k = 0; k < nv; ++k) r = std::max(r, std::max(std::fabs(a[k]), std::fabs(c[k])) / b[k]);
+    if (r < 1e-18L) break;
+    if (levels == LINE_MAX_LEVELS) { chain.clear(); red.clear(); return; }
+    const int64_t s = int64_t(1) << levels;
+    std::vector<double> al(nv, 0.0), ga(nv, 0.0);
+    for (int64_t k = 0; k < nv; ++k) {
+      const int64_t kl = loop ? ((k - s) % nv + nv) % nv : k - s, kr = loop ? (k + s) % nv : k + s;
+      ld x = 0.0L, y = 0.0L;
+      b2[k] = b[k];
+      a2[k] = c2[k] = 0.0L;
+      if (kl >= 0) {
+        x = -a[k] / b[kl];
+        b2[k] += x * c[kl];
+        a2[k] = x * a[kl];
+      }
+      if (kr < nv) {
+        y = -c[k] / b[kr];
+        b2[k] += y * a[kr];
+        c2[k] = y * c[kr];
+      }
+      al[k] = static_cast<double>(x);
+      ga[k] = static_cast<double>(y);
+    }
+    a.swap(a2);
+    b.swap(b2);
+    c.swap(c2);
+    red.insert(red.end(), al.begin(), al.end());
+    red.insert(red.end(), ga.begin(), ga.end());
+  }
+  for (int64_t k = 0; k < nv; ++k) red.push_back(static_cast<double>(1.0L / b[k]));
+  m->chain_nv = nv;
+  m->chain_loop = loop ? 1 : 0;
+  m->line_levels = levels;
 }
 
 static void free_mesh(cvw_mesh* m) {
@@ -1178,6 +1389,7 @@ static void free_mesh(cvw_mesh* m) {
   (void)hipFree(m->d_tens);
   (void)hipFree(m->d_lanes);
   (void)hipFree(m->d_cell_dof);
+  (void)hipFree(m->d_cell_dof_t);
   (void)hipFree(m->d_dof_ptr);
   (void)hipFree(m->d_dof_ent);
   (void)hipFree(m->d_geo);
@@ -1196,6 +1408,11 @@ static void free_mesh(cvw_mesh* m) {
   (void)hipFree(m->d_nbrt);
   (void)hipFree(m->d_dinv_f);
   (void)hipFree(m->d_dinv_d);
+  (void)hipFree(m->d_dof_ent4);
+  (void)hipFree(m->d_line_nb);
+  (void)hipFree(m->d_chain);
+  (void)hipFree(m->d_line_red);
+  (void)hipFree(m->d_line_int);
   delete m;
 }
 
@@ -1518,6 +1735,23 @@ cvw_status cvw_mesh_build(const cvw_mesh_desc* d, cvw_mesh** out) {
     if ((st = upload(&m->d_nbr, dn)) != CVW_OK) { free_mesh(m); return st; }
   }
   if ((st = upload(&m->d_cell_dof, m->h_cell_dof)) != CVW_OK) { free_mesh(m); return st; }
+  if (d->space == CVW_CG && d->cell == CVW_QUAD) {
+    std::vector<int32_t> t(m->h_cell_dof.size());
+    for (int64_t e = 0; e < E; ++e)
+      for (int j = 0; j < m->nloc; ++j) t[j * E + e] = m->h_cell_dof[e * m->nloc + j];
+    std::vector<int4> e4(m->ndof, int4{-1, -1, -1, -1});
+    for (int64_t i = 0; i < m->ndof; ++i) {
+      int32_t* o = &e4[i].x;
+      const int32_t k = dptr[i + 1] - dptr[i];
+      if (k > 4) o[0] = -2;
+      else
+        for (int32_t c = 0; c < k; ++c) {
+          const int64_t e = dent[dptr[i] + c] / m->nloc;
+          o[c] = static_cast<int32_t>((dent[dptr[i] + c] - e * m->nloc) * E + e);
+        }
+    }
+    if ((st = upload(&m->d_cell_dof_t, t)) != CVW_OK || (st = upload(&m->d_dof_ent4, e4)) != CVW_OK) { free_mesh(m); return st; }
+  }
   if ((st = upload(&m->d_dof_ptr, dptr)) != CVW_OK) { free_mesh(m); return st; }
   if ((st = upload(&m->d_dof_ent, dent)) != CVW_OK) { free_mesh(m); return st; }
   if ((st = upload(&m->d_geo, geo)) != CVW_OK) { free_mesh(m); return st; }
@@ -1537,6 +1771,14 @@ cvw_status cvw_mesh_build(const cvw_mesh_desc* d, cvw_mesh** out) {
     for (int64_t e = 0; e < E; ++e)
       if (!(hc[e] > 0)) { free_mesh(m); set_error("segment cells must have x1 > x0"); return CVW_EINVAL; }
     if ((st = upload(&m->d_hcell, hc)) != CVW_OK) { free_mesh(m); return st; }
+    std::vector<int32_t> lnb(2 * E, -1);
+    for (int64_t v = 0; v < Nv; ++v)
+      if (cnt[v] == 2)
+        for (int k = 0; k < 2; ++k) {
+          const int64_t i = m->h_vtx_ptr[v] + k;
+          lnb[2 * m->h_vtx_cell[i] + m->h_vtx_lv[i]] = m->h_vtx_cell[m->h_vtx_ptr[v] + 1 - k];
+        }
+    if ((st = upload(&m->d_line_nb, lnb)) != CVW_OK) { free_mesh(m); return st; }
     std::vector<SegTables> t1(1);
     fill_seg_tables(t1[0], std::min(p, MAXP), d->space == CVW_CG);
     if ((st = upload(&m->d_segt, t1)) != CVW_OK) { free_mesh(m); return st; }
@@ -1647,6 +1889,15 @@ cvw_status cvw_mesh_build(const cvw_mesh_desc* d, cvw_mesh** out) {
       if ((st = upload(&m->d_dinv_d, inv_d)) != CVW_OK) { free_mesh(m); return st; }
       if ((st = upload(&m->d_dinv_f, inv_f)) != CVW_OK) { free_mesh(m); return st; }
     }
+  }
+  if (d->space == CVW_CG && d->cell == CVW_QUAD && m->n_mass > 0) m->mass_cond = quad_mass_condition(m, d);
+  if (d->space == CVW_CG && d->cell == CVW_SEG && p <= LINE_DIRECT_MAXP) {
+    std::vector<int32_t> chain;
+    std::vector<double> red, tab;
+    line_mass_operator(m, d, chain, red, tab);
+    if (m->line_levels >= 0 &&
+        ((st = upload(&m->d_chain, chain)) != CVW_OK || (st = upload(&m->d_line_red, red)) != CVW_OK ||
+         (st = upload(&m->d_line_int, tab)) != CVW_OK)) { free_mesh(m); return st; }
   }
   {
     std::vector<TensorTables> t1(1, m->tens);
@@ -2024,6 +2275,12 @@ static cvw_status learned_audit(const cvw_mesh* m, const cvw_params* prm, const 
   return dgquad_audit_finalize(m, w.apart, prm->audit_tol, w.status, w.aout, s);
 }
 
+// whether an evaluation goes through the vertex candidates in the workspace
+// (the line kernels form those of a cell's two vertices themselves)
+static bool needs_candidates(const cvw_mesh* m, const cvw_params* prm) {
+  return prm->sensor != CVW_SENSOR_FIXED && m->cell != CVW_SEG;
+}
+
 static cvw_status candidates_any(const cvw_mesh* m, const cvw_params* prm, const void* u, void* cand,
                                  hipStream_t s) {
   if (m->cell == CVW_SEG) return seg_candidates(m, prm, u, cand, s);
@@ -2061,7 +2318,7 @@ cvw_status cvw_sensor(const cvw_mesh* m, const cvw_params* prm, const void* u, v
                        static_cast<float*>(alpha), nullptr, w.status, 0.f, 0.f, 0.f, s,
                        static_cast<const float*>(gamma));
   }
-  if (prm->sensor != CVW_SENSOR_FIXED) {
+  if (needs_candidates(m, prm)) {
     st = candidates_any(m, prm, u, w.cand, s);
     if (st != CVW_OK) return st;
   }
@@ -2074,7 +2331,7 @@ cvw_status cvw_sensor(const cvw_mesh* m, const cvw_params* prm, const void* u, v
                        static_cast<const float*>(gamma));
   }
   if (m->cell == CVW_SEG)
-    return seg_eval(m, prm, MODE_SENSOR, u, w.cand, w.pg, w.rcell, nullptr, gamma, alpha, w.status, s);
+    return seg_eval(m, prm, MODE_SENSOR, u, nullptr, w.rcell, nullptr, gamma, alpha, w.status, s);
   if (m->cell == CVW_TET)
     return tet_eval(m, prm, MODE_SENSOR, static_cast<const float*>(u), nullptr, nullptr, static_cast<float*>(gamma),
                     static_cast<float*>(alpha), static_cast<const float*>(w.cand), w.gam, w.status, 0.f, 0.f, 0.f, s);
@@ -2224,13 +2481,13 @@ cvw_status cvw_residual(const cvw_mesh* m, const cvw_params* prm, const void* u,
     return dgquad_eval(m, prm, MODE_RESIDUAL, static_cast<const float*>(u), nullptr, static_cast<float*>(R),
                        static_cast<float*>(gamma_out), nullptr, nullptr, w.status, 0.f, 0.f, 0.f, s, w.gam);
   }
-  if (prm->sensor != CVW_SENSOR_FIXED) {
+  if (needs_candidates(m, prm)) {
     st = candidates_any(m, prm, u, w.cand, s);
     if (st != CVW_OK) return st;
   }
   if (prm->sensor == CVW_SENSOR_LEARNED && (st = learned_gamma(m, prm, u, w.cand, w, s)) != CVW_OK) return st;
   if (m->cell == CVW_SEG)
-    return seg_eval(m, prm, MODE_RESIDUAL, u, w.cand, w.pg, w.rcell, R, gamma_out, nullptr, w.status, s);
+    return seg_eval(m, prm, MODE_RESIDUAL, u, nullptr, w.rcell, R, gamma_out, nullptr, w.status, s);
   if (m->cell == CVW_TET)
     return tet_eval(m, prm, MODE_RESIDUAL, static_cast<const float*>(u), nullptr, static_cast<float*>(R),
                     static_cast<float*>(gamma_out), nullptr, static_cast<const float*>(w.cand), w.gam, w.status, 0.f,
@@ -2256,36 +2513,45 @@ cvw_status cvw_residual(const cvw_mesh* m, const cvw_params* prm, const void* u,
 
 namespace {
 
-// Mass-matrix tolerances of the PCG solve (relative, preconditioned norm) and
-// its launch-time iteration cap; converged iterations are no-ops on the device.
-constexpr double PCG_TOL_F32 = 2e-7, PCG_TOL_F64 = 1e-14;
-constexpr int PCG_MAXIT_F32 = 64, PCG_MAXIT_F64 = 160;
-
 template <typename Real>
 cvw_status generic_stage(const cvw_mesh* m, const cvw_params* prm, const WS& w, const Real* us, const Real* cand,
                          const Real* un, Real* uo, double dt, double a0, double b0, hipStream_t s) {
   cvw_status st;
-  Real* rhs = static_cast<Real*>(w.rhs);
+  // the direct line solve and the quadrilaterals' conjugate gradients start from
+  // the element rows; the line's conjugate gradients need them assembled
+  const bool direct = m->cell == CVW_SEG && m->space == CVW_CG && m->line_levels >= 0;
+  const bool quad = m->cell == CVW_QUAD;
+  Real* rhs = direct || quad ? nullptr : static_cast<Real*>(w.rhs);
+  if (m->cell == CVW_SEG && m->space == CVW_DG)        // diagonal mass: the cell kernel updates the state
+    return seg_eval(m, prm, MODE_STAGE, us, cand, nullptr, uo, nullptr, nullptr, w.status, s, LineStage{un, a0, b0, dt});
+  if (direct && (st = line_clear_rows(m, w.status, s)) != CVW_OK) return st;
   if (m->cell == CVW_SEG)
-    st = seg_eval(m, prm, MODE_RESIDUAL, us, cand, w.pg, w.rcell, rhs, nullptr, nullptr, w.status, s);
+    st = seg_eval(m, prm, MODE_RESIDUAL, us, cand, w.rcell, rhs, nullptr, nullptr, w.status, s);
   else
     st = cgquad_eval(m, prm, MODE_RESIDUAL, reinterpret_cast<const float*>(us), reinterpret_cast<const float*>(cand),
-                     static_cast<float*>(w.pg), static_cast<float*>(w.rcell), reinterpret_cast<float*>(rhs), nullptr,
-                     nullptr, w.status, s);
+                     static_cast<float*>(w.pg), static_cast<float*>(w.rcell), nullptr, nullptr, nullptr, w.status, s);
   if (st != CVW_OK) return st;
+  if (direct)
+    return line_mass_stage<Real>(m, n_var(m, prm->flux), static_cast<const Real*>(w.rcell), us, un, uo, a0, b0, dt,
+                                 w.status + WS_CG_ROWS, s);
+  if (quad) {
+    // z and p together hold the pairs, R and x the second ones (then x goes to the
+    // projected gradient's place); the second partials take the place of the totals
+    const QuadSolve q{static_cast<float*>(w.rcell), static_cast<float2*>(w.z), static_cast<float2*>(w.rhs),
+                      static_cast<float*>(w.x), static_cast<float*>(w.pg), static_cast<float*>(w.r), static_cast<float*>(w.Ap),
+                      {w.part, w.tot}, w.S, TOT_SCRATCH / sizeof(double)};
+    return cgquad_mass_stage(m, static_cast<const float*>(w.rcell), q, PCG_TOL_F32, PCG_MAXIT_F32,
+                             reinterpret_cast<const float*>(us), reinterpret_cast<const float*>(un),
+                             reinterpret_cast<float*>(uo), a0, b0, dt, w.status, s);
+  }
   const bool f64 = std::is_same<Real, double>::value;
   const Real* dinv = f64 ? reinterpret_cast<const Real*>(m->d_dinv_d) : reinterpret_cast<const Real*>(m->d_dinv_f);
-  const int64_t n = static_cast<int64_t>(state_elems(m, n_var(m, prm->flux)));
-  if (m->space == CVW_CG) {
-    Real* x = static_cast<Real*>(w.x);
-    st = cg_mass_solve<Real>(m, rhs, x, static_cast<Real*>(w.r), static_cast<Real*>(w.z), static_cast<Real*>(w.p),
-                             static_cast<Real*>(w.Ap), static_cast<Real*>(w.rcell), w.part, w.S, dinv,
-                             f64 ? PCG_TOL_F64 : PCG_TOL_F32, f64 ? PCG_MAXIT_F64 : PCG_MAXIT_F32, w.status, s,
-                             n_var(m, prm->flux));
-    if (st != CVW_OK) return st;
-    return stage_update<Real>(us, un, x, nullptr, uo, a0, b0, dt, n, s);
-  }
-  return stage_update<Real>(us, un, rhs, dinv, uo, a0, b0, dt, n, s, m->n_mass);
+  Real* x = static_cast<Real*>(w.x);
+  st = line_pcg<Real>(m, rhs, x, static_cast<Real*>(w.r), static_cast<Real*>(w.z), static_cast<Real*>(w.p),
+                      static_cast<Real*>(w.Ap), static_cast<Real*>(w.rcell), dinv, f64 ? PCG_TOL_F64 : PCG_TOL_F32,
+                      f64 ? PCG_MAXIT_F64 : PCG_MAXIT_F32, w.status, s, n_var(m, prm->flux));
+  if (st != CVW_OK) return st;
+  return stage_update<Real>(us, un, x, uo, a0, b0, dt, static_cast<int64_t>(state_elems(m, n_var(m, prm->flux))), s);
 }
 
 cvw_status any_stage(const cvw_mesh* m, const cvw_params* prm, const WS& w, const void* us, const void* cand,
@@ -2381,11 +2647,9 @@ cvw_status cvw_step(const cvw_mesh* m, const cvw_params* prm, void* u, double dt
         (st = learned_audit(m, prm, u, w, s)) != CVW_OK)
       return st;
     for (const auto& sg : stages) {
-      if (prm->sensor != CVW_SENSOR_FIXED && !use_tile(m, prm)) {
-        st = candidates_any(m, prm, sg.in, w.cand, s);
-        if (st != CVW_OK) return st;
-      }
-      st = any_stage(m, prm, w, sg.in, w.cand, u, sg.out, dt, sg.a0, sg.b0, s);
+      const bool cand = needs_candidates(m, prm) && !use_tile(m, prm);
+      if (cand && (st = candidates_any(m, prm, sg.in, w.cand, s)) != CVW_OK) return st;
+      st = any_stage(m, prm, w, sg.in, m->cell == CVW_SEG ? nullptr : w.cand, u, sg.out, dt, sg.a0, sg.b0, s);
       if (st != CVW_OK) return st;
     }
   }

@@ -18,6 +18,9 @@ enum : uint32_t { ST_NONFINITE = 1u, ST_NONPOSITIVE = 2u, ST_PCG_STALL = 4u, ST_
 // cells the learned sensor handed to the plain one since the last poll, word 2
 // the audit latch (nonzero: the plain sensor takes every cell)
 enum { WS_STATUS = 0, WS_FALLBACK_COUNT = 1, WS_LEARNED_OFF = 2 };
+// from word 8, one word per variable of a CG line's stage: 1 a NaN, 2 an infinity
+// among the element rows (line_clear_rows; needed only where several blocks solve)
+enum { WS_CG_ROWS = 8, CG_ROWS_NAN = 1, CG_ROWS_INF = 2 };
 // modes of the fused sensor pass
 enum : int { TILE_ALL = 0, TILE_FALLBACK = 1, TILE_AUDIT = 2 };
 
@@ -330,7 +333,7 @@ struct SegHPArgs {
   const double* tab;                // hp_off(p) layout
   const int32_t* cell_dof;          // CG [E][p+1]
   const int32_t* cell_vtx;          // [E][2]
-  const int32_t* nbr;               // DG [E][2] face neighbours
+  const int32_t* nb;                // [E][2] the cells across the left and right vertex (-1: an end)
   const double* hcell;              // [E] cell lengths
   const int32_t* vptr;              // vertex patches (CSR, entries cell * 4 + local vertex)
   const int32_t* vent;
@@ -373,6 +376,8 @@ struct cvw_mesh {
   cvw::LaneRec* d_lanes = nullptr;   // [16] DG quadrilateral lane tables
   // CG
   int32_t* d_cell_dof = nullptr;     // [E][nloc]
+  int32_t* d_cell_dof_t = nullptr;   // CG quadrilaterals: the same, [nloc][E] (lanes on neighbouring cells read neighbouring entries)
+  int4* d_dof_ent4 = nullptr;        // CG quadrilaterals: [ndof] the patch of each DOF as node * E + cell (-1: none; .x = -2: more than four)
   int32_t* d_dof_ptr = nullptr;      // [ndof + 1] CSR of the DOF patches
   int32_t* d_dof_ent = nullptr;      // [E * nloc] cell * nloc + local node, ascending (cell, node)
   float* d_geo = nullptr;            // [E][8] vertex 0 and the other vertices relative to it
@@ -400,6 +405,19 @@ struct cvw_mesh {
   float* d_dinv_f = nullptr;          // [n_mass]
   double* d_dinv_d = nullptr;         // [n_mass]
   int64_t n_mass = 0;
+  // CG quadrilaterals: condition number of the mass matrix scaled by the lumped
+  // one (a bound from the element matrices; 0: none), which bounds the
+  // conjugate gradient iterations that a solve can take
+  double mass_cond = 0;
+  // CG lines: the cells in chain order, the eliminated vertex system (cyclic
+  // reduction factors [levels][2][chain_nv], inverse diagonal [chain_nv]) and
+  // the interior tables; line_levels < 0: no single chain, conjugate gradients
+  int32_t* d_line_nb = nullptr;       // lines: [E][2] the cell across the left / right vertex (-1: an end)
+  int32_t* d_chain = nullptr;
+  double* d_line_red = nullptr;
+  double* d_line_int = nullptr;
+  int64_t chain_nv = 0;
+  int chain_loop = 0, line_levels = -1;
 };
 
 namespace cvw {
@@ -442,18 +460,24 @@ cvw_status cgquad_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const
                        hipStream_t s);
 // kernel launchers (cvw_seg.hip)
 cvw_status seg_candidates(const cvw_mesh* m, const cvw_params* prm, const void* u, void* cand, hipStream_t s);
-cvw_status seg_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const void* u, const void* cand, void* pg,
-                    void* rcell, void* R, void* gamma, void* alpha, uint32_t* status, hipStream_t s);
+// cand null: the cell kernel evaluates the vertex candidates itself.  CG: the
+// element rows go to rcell and, when R is given, are assembled there; DG:
+// residual or (MODE_STAGE, lst) stage result in R
+struct LineStage {
+  const void* un = nullptr;
+  double a0 = 0, b0 = 0, dt = 0;
+};
+cvw_status seg_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const void* u, const void* cand, void* rcell,
+                    void* R, void* gamma, void* alpha, uint32_t* status, hipStream_t s, const LineStage& lst = {});
 // 1D elements of any degree in float64, systems and lines with ends
 // (cvw_seghp.hip): the candidates of the sensor variable [Nv][p] and the
-// evaluation (modes as seg_eval; pg [nv][ndof] and rcell [nv][E][p+1] are CG
-// scratch)
+// evaluation (as seg_eval; rcell [nv][E][p+1] is CG scratch)
 bool seg_hp(const cvw_mesh* m, const cvw_params* prm);
 SegHPArgs seghp_args(const cvw_mesh* m, const cvw_params* prm);
 cvw_status seghp_candidates(const cvw_mesh* m, const cvw_params* prm, const double* u, double* cand, hipStream_t s);
 cvw_status seghp_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const double* u, const double* cand,
-                      double* pg, double* rcell, double* R, double* gamma, double* alpha, uint32_t* status,
-                      hipStream_t s);
+                      double* rcell, double* R, double* gamma, double* alpha, uint32_t* status, hipStream_t s,
+                      const LineStage& lst);
 // batched fused sensor pass over (instance, tile) items of degree P
 // (cvw_dgsensor.hip), and the tile arguments of a mesh
 cvw_status batch_sensor_pass(int P, const BatchInst* inst, const int2* items, int n_items, int stage, int grid,
@@ -484,16 +508,37 @@ cvw_status tri_totals(const cvw_mesh* m, int nvar, const float* u, double* parti
 
 // time stepping (cvw_cgstep.hip)
 size_t pcg_partials(int64_t n);
-// M x = b for every variable: lines solve all nvar variables at once (vectors
-// [nvar][ndof], ycell [nvar][E][n_loc]); quadrilaterals one variable (nvar 1)
+// M x = b on a line by conjugate gradients, every variable (vectors
+// [nvar][ndof], ycell [nvar][E][n_loc])
 template <typename Real>
-cvw_status cg_mass_solve(const cvw_mesh* m, const Real* b, Real* x, Real* r, Real* z, Real* p, Real* Ap,
-                         Real* ycell, double* part, double* S, const Real* dinv, double tol, int maxit,
-                         uint32_t* status, hipStream_t s, int nvar = 1);
-// dinv (a diagonal mass of nm entries, shared by the variables) or null
+cvw_status line_pcg(const cvw_mesh* m, const Real* b, Real* x, Real* r, Real* z, Real* p, Real* Ap, Real* ycell,
+                    const Real* dinv, double tol, int maxit, uint32_t* status, hipStream_t s, int nvar);
+// CG stages u_out = a0 u_n + b0 (u_s - dt M^{-1} R) from the element rows.
+// Quadrilaterals: conjugate gradients with the lumped mass as preconditioner
+// (scratch: QuadSolve); lines of low degree: the direct solve (m->line_levels >= 0;
+// line_clear_rows comes before the cell kernel; rows_flag: the WS_CG_ROWS words)
+struct QuadSolve {
+  float* y;                 // [E n_loc] element rows of M p, or quadrature weights; may be the element rows of R
+  float2* pz;               // [ndof] pairs (direction, preconditioned residual)
+  float2* pz2;              // the same once more (may overlap x)
+  float* x;                 // [ndof] result; with pz2 in use x2
+  float* x2;
+  float* r;
+  float* Ap;
+  double* part[2];          // [pcg_partials] block partials of r.z and of p.Ap
+  double* S;                // 8 scalars
+  size_t part_cap;          // entries of part[1]
+};
+cvw_status cgquad_mass_stage(const cvw_mesh* m, const float* rcell, const QuadSolve& q, double tol, int maxit,
+                             const float* us, const float* un, float* uo, double a0, double b0, double dt,
+                             uint32_t* status, hipStream_t s);
+cvw_status line_clear_rows(const cvw_mesh* m, uint32_t* status, hipStream_t s);
 template <typename Real>
-cvw_status stage_update(const Real* us, const Real* un, const Real* x, const Real* dinv, Real* uo, double a0,
-                        double b0, double dt, int64_t n, hipStream_t s, int64_t nm = 0);
+cvw_status line_mass_stage(const cvw_mesh* m, int nvar, const Real* rcell, const Real* us, const Real* un, Real* uo,
+                           double a0, double b0, double dt, const uint32_t* rows_flag, hipStream_t s);
+template <typename Real>
+cvw_status stage_update(const Real* us, const Real* un, const Real* x, Real* uo, double a0, double b0, double dt,
+                        int64_t n, hipStream_t s);
 cvw_status totals_f32(const cvw_mesh* m, int nvar, const float* u, double* partial, double* out_dev,
                       hipStream_t s);
 

@@ -16,14 +16,18 @@
 //    the vertex, pointwise smoothness indicator (eq. pointsnorm), Jiang-Shu
 //    weights and the vertex candidate (eq. taylorcand).  The patch of an end
 //    vertex is its one cell.
-//  * hp_pg_kernel       -- CG: P_h u' at the DOFs, every variable.
-//  * hp_cell_kernel     -- element semi-norms of the cell and of its two
+//    Only for callers that ask for the candidates themselves.
+//  * hp_cell_kernel     -- the candidates of the cell's two vertices (unless
+//    the caller gives them), CG: P_h u' at its nodes, both from the values of
+//    the cell and its two neighbours in LDS (a launch costs more than
+//    evaluating the neighbours again: DG P8 on 4096 cells, Euler, a step of 9
+//    launches 145.6 us, of 3 launches 124.4 us); element semi-norms of the cell and of its two
 //    vertex Taylor candidates (eq. snorm), the reconstruction weights and
 //    gamma_e (eqs. finalweno, gamma), lambda_e and nu_e (eq. lostab),
 //    alpha_q (eqs. dissrateorig to alpha_prelim), the element residual (eq.
-//    sdstab) with interface and boundary fluxes.
+//    sdstab) with interface and boundary fluxes; DG: the stage update.
 //  * hp_assemble_kernel -- CG: R_I = sum of the element rows sharing I.
-// (The CG mass solve of a line runs in one workgroup, cvw_cgstep.hip.)
+// (The CG mass solve of a line with its stage update: cvw_cgstep.hip.)
 #include "cvw_device.h"
 
 namespace cvw {
@@ -124,6 +128,33 @@ __device__ __forceinline__ int64_t hp_idx(const SegHPArgs& A, int64_t e, int j) 
 
 }  // namespace
 
+// One cell's part of a vertex candidate: lane k - 1 adds w D^k s of the cell's
+// nodal values sv (LDS) at its local vertex lv to acc, and w to wsum
+__device__ __forceinline__ void hp_hermite(const SegHPArgs& A, const double* sv, int lv, double h, int k, double& acc,
+                                           double& wsum) {
+  const int p = A.p, n1 = p + 1;
+  const HPOff o = hp_off(p);
+  double H = 0.0, hH = 0.0;
+  if (k <= p) {
+    // derivatives annihilate constants: take them of the data relative to its first node
+    const double u0 = sv[0];
+#pragma unroll 8
+    for (int j = 0; j < n1; ++j) H = fma(A.tab[o.DV + (lv * n1 + j) * n1 + k], sv[j] - u0, H);
+    hH = ipow(2.0, k) * H;                 // h^k D^k s = 2^k d^k s / dxi^k
+    H *= ipow(2.0 / h, k);
+  }
+  const double beta = sqrt(wave_sum(hH * hH));
+  double w;
+  if (A.ms.fast_exp) {
+    const double den = A.ms.eps_vd + beta;
+    w = 1.0 / (den * den);
+  } else {
+    w = pow(A.ms.eps_vd + pow(beta, static_cast<double>(A.ms.q_beta)), -static_cast<double>(A.ms.r));
+  }
+  acc = fma(w, H, acc);
+  wsum += w;
+}
+
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void hp_vertex_kernel(SegHPArgs A, const double* __restrict__ u,
                                                        double* __restrict__ cand) {
@@ -131,7 +162,6 @@ __global__ __launch_bounds__(64) void hp_vertex_kernel(SegHPArgs A, const double
   const int64_t i = blockIdx.x;
   const int lane = threadIdx.x;
   const int p = A.p, n1 = p + 1;
-  const HPOff o = hp_off(p);
   const int k = lane + 1;                 // derivative order held by this lane
   double acc = 0.0, wsum = 0.0;
   for (int it = A.vptr[i]; it < A.vptr[i + 1]; ++it) {
@@ -141,60 +171,20 @@ __global__ __launch_bounds__(64) void hp_vertex_kernel(SegHPArgs A, const double
     __syncthreads();
     if (lane < n1) su[lane] = u[hp_idx(A, e, lane)];
     __syncthreads();
-    const double h = A.hcell[e];
-    double H = 0.0, hH = 0.0;
-    if (k <= p) {
-      // derivatives annihilate constants: take them of the data relative to its first node
-      const double u0 = su[0];
-#pragma unroll 8
-      for (int j = 0; j < n1; ++j) H = fma(A.tab[o.DV + (lv * n1 + j) * n1 + k], su[j] - u0, H);
-      hH = ipow(2.0, k) * H;               // h^k D^k s = 2^k d^k s / dxi^k
-      H *= ipow(2.0 / h, k);
-    }
-    const double beta = sqrt(wave_sum(hH * hH));
-    double w;
-    if (A.ms.fast_exp) {
-      const double den = A.ms.eps_vd + beta;
-      w = 1.0 / (den * den);
-    } else {
-      w = pow(A.ms.eps_vd + pow(beta, static_cast<double>(A.ms.q_beta)), -static_cast<double>(A.ms.r));
-    }
-    acc = fma(w, H, acc);
-    wsum += w;
+    hp_hermite(A, su, lv, A.hcell[e], k, acc, wsum);
   }
   if (k <= p) cand[i * p + lane] = acc / wsum;
 }
 
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void hp_pg_kernel(SegHPArgs A, const double* __restrict__ u,
-                                                    double* __restrict__ pg) {
-  const int64_t I = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (I >= A.ndof) return;
-  const int n1 = A.p + 1;
-  const HPOff o = hp_off(A.p);
-  const int beg = A.dptr[I], end = A.dptr[I + 1];
-  for (int v = 0; v < A.nv; ++v) {
-    const double* uv = u + v * A.ndof;
-    double g = 0.0;
-    for (int it = beg; it < end; ++it) {
-      const int ent = A.dent[it];
-      const int64_t e = ent / n1;
-      const int a = ent - static_cast<int>(e) * n1;
-      double d = 0.0;
-      for (int j = 0; j < n1; ++j) d = fma(A.tab[o.DN + a * n1 + j], uv[A.cell_dof[e * n1 + j]], d);
-      g += d * (2.0 / A.hcell[e]);
-    }
-    pg[v * A.ndof + I] = g / (end - beg);
-  }
-}
-
-// ---------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* __restrict__ u,
-                                                     const double* __restrict__ cand, const double* __restrict__ pg,
-                                                     int mode, double* __restrict__ rout,
-                                                     double* __restrict__ gamma_out, double* __restrict__ alpha_out,
-                                                     uint32_t* __restrict__ status) {
+                                                     const double* __restrict__ cand, int mode,
+                                                     double* __restrict__ rout, double* __restrict__ gamma_out,
+                                                     double* __restrict__ alpha_out, uint32_t* __restrict__ status,
+                                                     const double* un, const double* __restrict__ dinv, double a0,
+                                                     double b0, double dt) {
   __shared__ double su[3][N1MAX];         // the cell's nodal values, every variable
+  __shared__ double sn[2][3][N1MAX];      // those of its left and right neighbour
   __shared__ double spg[3][N1MAX];        // CG: P_h u' at the cell's nodes
   __shared__ double sc[2][HP_MAXP];       // vertex candidates (physical derivatives 1..p)
   __shared__ double sG[3][N1MAX];         // w_q times the volume integrand at the Gauss points
@@ -206,21 +196,75 @@ __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* 
   const HPOff o = hp_off(p);
   const bool plain = A.ms.sensor_kind != CVW_SENSOR_FIXED;
   const int64_t vstride = A.cg ? A.ndof : A.E * n1;
+  // the cell across each vertex (-1: an end of the line): the left vertex is
+  // the right one of the left neighbour and the other way round
+  int en[2], first[2];
+  double hn[2];
+#pragma unroll
+  for (int l = 0; l < 2; ++l) {
+    en[l] = A.nb[e * 2 + l];
+    first[l] = en[l] < 0 || static_cast<int>(e) < en[l];   // the own cell comes first in the patch
+    hn[l] = en[l] >= 0 ? A.hcell[en[l]] : 1.0;
+  }
   if (lane < n1) {
-    const int64_t ix = hp_idx(A, e, lane);
+    const int64_t ix = hp_idx(A, e, lane), il = en[0] >= 0 ? hp_idx(A, en[0], lane) : ix,
+                  ir = en[1] >= 0 ? hp_idx(A, en[1], lane) : ix;
 #pragma unroll
     for (int v = 0; v < 3; ++v) {
       if (v >= nv) break;
       su[v][lane] = u[v * vstride + ix];
-      if (A.cg) spg[v][lane] = pg[v * A.ndof + ix];
+      sn[0][v][lane] = u[v * vstride + il];
+      sn[1][v][lane] = u[v * vstride + ir];
     }
   }
-  if (plain && lane < p) {
+  if (plain && cand && lane < p) {
     sc[0][lane] = cand[static_cast<int64_t>(A.cell_vtx[e * 2]) * p + lane];
     sc[1][lane] = cand[static_cast<int64_t>(A.cell_vtx[e * 2 + 1]) * p + lane];
   }
   __syncthreads();
   const double h = A.hcell[e], s = 2.0 / h;
+  if (plain && !cand) {
+#pragma unroll
+    for (int l = 0; l < 2; ++l) {
+      double acc = 0.0, wsum = 0.0;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {       // the patch in ascending (cell, local vertex) order
+        const bool own = (c == 0) == (first[l] != 0);
+        if (own || en[l] >= 0)
+          hp_hermite(A, own ? su[0] : sn[l][0], own ? l : 1 - l, own ? h : hn[l], lane + 1, acc, wsum);
+      }
+      if (lane < p) sc[l][lane] = acc / wsum;
+    }
+  }
+  if (A.cg && lane < n1) {
+    const int a = lane, side = a == 0 ? 0 : 1;
+    const bool shared = (a == 0 || a == p) && (side == 0 ? en[0] : en[1]) >= 0;
+    double g[3] = {0.0, 0.0, 0.0}, go[3] = {0.0, 0.0, 0.0};
+    for (int j = 0; j < n1; ++j) {
+      const double d = A.tab[o.DN + a * n1 + j];
+#pragma unroll
+      for (int v = 0; v < 3; ++v)
+        if (v < nv) g[v] = fma(d, su[v][j], g[v]);
+    }
+    if (shared)
+      for (int j = 0; j < n1; ++j) {
+        const double d = A.tab[o.DN + (p - a) * n1 + j];
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+          if (v < nv) go[v] = fma(d, sn[side][v][j], go[v]);
+      }
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+      if (v >= nv) break;
+      double r = g[v] * s;
+      if (shared) {                       // ascending cell order
+        const double w = 2.0 / (side == 0 ? hn[0] : hn[1]);
+        r = ((side == 0 ? first[0] : first[1]) ? fma(go[v], w, r) : fma(g[v], s, go[v] * w)) / 2.0;
+      }
+      spg[v][a] = r;
+    }
+  }
+  __syncthreads();
   const bool qok = lane < n1;
   const int q = qok ? lane : 0;
   const double xq = A.tab[o.xq + q], wq = A.tab[o.wq + q];
@@ -346,8 +390,7 @@ __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* 
   // ---- interface and boundary fluxes ----
   if (lane < 2) {
     const int fc = lane;
-    const int32_t vid = A.cell_vtx[e * 2 + fc];
-    const bool at_end = A.vptr[vid + 1] - A.vptr[vid] == 1;
+    const bool at_end = (fc == 0 ? en[0] : en[1]) < 0;
     const double n = fc == 0 ? -1.0 : 1.0;
     double um[3] = {0.0, 0.0, 0.0}, up[3] = {0.0, 0.0, 0.0};
     for (int j = 0; j < n1; ++j) {
@@ -361,12 +404,11 @@ __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* 
       hp_ghost(A, um, fc, up);
       has = 1;
     } else if (!A.cg) {
-      const int64_t en = A.nbr[e * 2 + fc];
       for (int j = 0; j < n1; ++j) {
         const double l = A.tab[o.DV + ((1 - fc) * n1 + j) * n1];
 #pragma unroll
         for (int v = 0; v < 3; ++v)
-          if (v < nv) up[v] = fma(l, u[v * vstride + en * n1 + j], up[v]);
+          if (v < nv) up[v] = fma(l, sn[fc][v][j], up[v]);
       }
       has = 1;
     }
@@ -391,8 +433,17 @@ __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* 
       for (int qq = 0; qq < n1; ++qq) r = fma(d1[qq], sG[v][qq], r);
       if (sHas[0]) r = fma(l0, sF[0][v], r);
       if (sHas[1]) r = fma(l1, sF[1][v], r);
-      bad = bad || !isfinite(r);
-      rout[v * A.E * n1 + e * n1 + j] = r;
+      if (!isfinite(r)) {
+        bad = true;
+        if (A.cg) atomicOr(status + WS_CG_ROWS + v, isnan(r) ? CG_ROWS_NAN : CG_ROWS_INF);
+      }
+      const int64_t i = v * A.E * n1 + e * n1 + j;
+      if (mode == MODE_STAGE && !A.cg) {
+        const double xi = r * dinv[e * n1 + j];
+        const double base = (a0 != 0.0) ? a0 * un[i] : 0.0;
+        r = base + b0 * (su[v][j] - dt * xi);
+      }
+      rout[i] = r;
     }
     if (bad) atomicOr(status, ST_NONFINITE);
   }
@@ -421,13 +472,13 @@ cvw_status seghp_candidates(const cvw_mesh* m, const cvw_params* prm, const doub
 }
 
 cvw_status seghp_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const double* u, const double* cand,
-                      double* pg, double* rcell, double* R, double* gamma, double* alpha, uint32_t* status,
-                      hipStream_t s) {
+                      double* rcell, double* R, double* gamma, double* alpha, uint32_t* status, hipStream_t s,
+                      const LineStage& lst) {
   const SegHPArgs A = seghp_args(m, prm);
-  if (A.cg) hipLaunchKernelGGL(hp_pg_kernel, dim3(nbh(m->ndof, 256)), dim3(256), 0, s, A, u, pg);
-  hipLaunchKernelGGL(hp_cell_kernel, dim3(static_cast<unsigned>(m->E)), dim3(64), 0, s, A, u, cand, pg, mode,
-                     A.cg ? rcell : R, gamma, alpha, status);
-  if (A.cg && mode != MODE_SENSOR)
+  hipLaunchKernelGGL(hp_cell_kernel, dim3(static_cast<unsigned>(m->E)), dim3(64), 0, s, A, u, cand, mode,
+                     A.cg ? rcell : R, gamma, alpha, status, static_cast<const double*>(lst.un), m->d_dinv_d, lst.a0,
+                     lst.b0, lst.dt);
+  if (A.cg && mode != MODE_SENSOR && R)      // R null: the caller takes the element rows
     hipLaunchKernelGGL(hp_assemble_kernel, dim3(nbh(m->ndof, 256)), dim3(256), 0, s, A, rcell, R);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
