@@ -889,23 +889,21 @@ __device__ __forceinline__ void dgq_eval_body_p1(
     atomicOr(status, (m1 ? ST_NONFINITE : 0u) | (m2 ? ST_NONPOSITIVE : 0u));
 }
 
-// 256-thread blocks: all loads in flight before the LDS stores
+// 256-thread blocks: both loads in flight before the LDS stores.  They stay in
+// named registers: a local array is turned into LDS of its own (15.9 KB per
+// block instead of 7.4), whose addressing reads the block size from the
+// dispatch packet in host memory -- 11 us per launch once 200 blocks or more
+// wait for it (cell pass on 67x45 Q2 cells 16.4 -> 5.5 us; a step of 16
+// meshes, 27 launches, 483 -> 270 us; 1024^2 Q3 Euler step 972 -> 939 us).
 __device__ __forceinline__ void load_lane_tables(const LaneRec* __restrict__ lanes, LaneRec* sl) {
   const float4* src = reinterpret_cast<const float4*>(lanes);
   float4* dst = reinterpret_cast<float4*>(sl);
   constexpr int n4 = 16 * sizeof(LaneRec) / 16;
-  constexpr int it = (n4 + 255) / 256;
-  float4 tmp[it];
-#pragma unroll
-  for (int k = 0; k < it; ++k) {
-    const int i = threadIdx.x + 256 * k;
-    if (i < n4) tmp[k] = src[i];
-  }
-#pragma unroll
-  for (int k = 0; k < it; ++k) {
-    const int i = threadIdx.x + 256 * k;
-    if (i < n4) dst[i] = tmp[k];
-  }
+  static_assert(n4 > 256 && n4 <= 512, "two loads per thread");
+  const int t = threadIdx.x, t2 = min(t + 256, n4 - 1);
+  const float4 a = src[t], b = src[t2];
+  dst[t] = a;
+  dst[t2] = b;  // the clamped threads store the same last record
 }
 
 #ifndef CVW_EVAL_WPE
