@@ -403,7 +403,7 @@ def bench_ensemble(torch, cvw, steps: int, tune: bool = True):
             grid = autotune.tune_batch(b, ws)
     out = {"workload": "64-instance DG ensemble, periodic n x n quads (n in [64, 512]), p in {1,2,3}, "
                        "advection / Burgers, SSP-RK3", "instances": len(items), "dofs": dofs, "steps": steps,
-           "blocks": grid if grid else "one per item"}
+           "blocks": grid if grid else "default"}
     for name, graph in (("graph", True), ("eager", False)):
         t = _timed(torch, stream, lambda: b.step(steps, ws, use_graph=graph), 1) / steps
         out[name] = {"value": 3.0 * dofs / t, "unit": "DOF-updates/s", "ms_per_step": t * 1e3}

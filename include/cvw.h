@@ -480,8 +480,9 @@ size_t cvw_batch_workspace_bytes(const cvw_batch* batch);
  * bitwise those of cvw_step on each instance alone. */
 cvw_status cvw_batch_step(cvw_batch* batch, int n_steps, int use_graph, void* ws, size_t ws_bytes, void* stream);
 
-/* Blocks per launch of the work-list kernels (grid-stride over the items);
- * <= 0 selects one block per item.  Invalidates a captured graph. */
+/* Blocks per work list (degree, or degree and flux) of the batched kernels,
+ * each walking a run of items; <= 0 selects the built-in number.  Results do
+ * not depend on it.  Invalidates a captured graph. */
 cvw_status cvw_batch_set_grid(cvw_batch* batch, int blocks);
 
 /* As cvw_poll_status, for the status word of a batch workspace. */

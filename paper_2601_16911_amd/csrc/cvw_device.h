@@ -481,4 +481,11 @@ __device__ __forceinline__ int64_t xcd_block(int64_t bid, int64_t nblocks_padded
   return (bid & 7) * per + (bid >> 3);
 }
 
+// the items of this block in a batch list whose first block is `first`
+struct BatchRun { int lo, hi; };
+__device__ __forceinline__ BatchRun batch_run(const BatchList& l, int first) {
+  const int64_t lo = xcd_block(static_cast<int>(blockIdx.x) - first, l.end - first) * l.run;
+  return {static_cast<int>(lo < l.n ? lo : l.n), static_cast<int>(lo + l.run < l.n ? lo + l.run : l.n)};
+}
+
 }  // namespace cvw

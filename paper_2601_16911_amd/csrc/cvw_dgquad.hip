@@ -1251,36 +1251,42 @@ cvw_status totals_f32(const cvw_mesh* m, int nvar, const float* u, double* part,
 namespace cvw {
 
 // ---------------------------------------------------------------------------
-// Batched stage over many independent meshes: per pass one launch per degree
-// covers every instance of that degree.  Work items (instance, block) are
-// walked by the blocks with a fixed stride; each item runs the same block body
-// as the single-mesh kernels, so results are bitwise those of the single-mesh
-// path.  The cell pass is launched once per (degree, flux) present.
+// Batched stage over many independent meshes: one launch per pass covers every
+// list of work items (instance, block), each walked by its blocks in runs;
+// each item runs the same block body as the single-mesh kernels, so
+// results are bitwise those of the single-mesh path.
 // ---------------------------------------------------------------------------
 template <int P>
-__global__ __launch_bounds__(256) void batch_vertex_kernel(const BatchInst* __restrict__ inst,
-                                                           const int2* __restrict__ items, int n_items,
-                                                           const TensorTables* __restrict__ tabs, int stage) {
-  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-    const int2 w = items[it];
+__device__ __forceinline__ void batch_vertex_list(const BatchInst* __restrict__ inst, const BatchList& l, int first,
+                                                  int stage) {
+  const BatchRun r = batch_run(l, first);
+  for (int it = r.lo; it < r.hi; ++it) {
+    const int2 w = l.items[it];
     const BatchInst& I = inst[w.x];
     dgq_vertex_body<P>(I.u_in[stage], I.cand, I.vptr, I.vent, I.Nv, w.y, I.vt, I.ms);
   }
 }
 
+__global__ __launch_bounds__(256) void batch_vertex_kernel(const BatchInst* __restrict__ inst, BatchLists L,
+                                                           int stage) {
+  int k = 0, first = 0;
+  while (static_cast<int>(blockIdx.x) >= L.l[k].end) first = L.l[k++].end;
+  const BatchList l = L.l[k];
+  switch (l.P) {
+    case 1: batch_vertex_list<1>(inst, l, first, stage); break;
+    case 2: batch_vertex_list<2>(inst, l, first, stage); break;
+    default: batch_vertex_list<3>(inst, l, first, stage); break;
+  }
+}
+
 template <int P, int FLUX>
-__global__ __launch_bounds__(256) void batch_eval_kernel(const BatchInst* __restrict__ inst,
-                                                         const int2* __restrict__ items, int n_items,
-                                                         const TensorTables* __restrict__ tabs,
-                                                         const LaneRec* __restrict__ lanes, int stage) {
-  __shared__ LaneRec sl[16];
-  load_lane_tables(lanes + 16 * P, sl);
-  __syncthreads();
+__device__ __forceinline__ void batch_eval_list(const BatchInst* __restrict__ inst, const BatchList& l, int first,
+                                                const TensorTables& tab, const LaneRec* sl, int stage) {
   const float A0[3] = {0.0f, 0.75f, 1.0f / 3.0f}, B0[3] = {1.0f, 0.25f, 2.0f / 3.0f};
   const float a0 = A0[stage], b0 = B0[stage];
-  const TensorTables& tab = tabs[P];
-  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-    const int2 w = items[it];
+  const BatchRun r = batch_run(l, first);
+  for (int it = r.lo; it < r.hi; ++it) {
+    const int2 w = l.items[it];
     const BatchInst& I = inst[w.x];
     if constexpr (P == 1)
       dgq_eval_body_p1<FLUX>(I.u_in[stage], I.u, I.u_out[stage], nullptr, nullptr, I.cand, I.cell_vtx, I.nbr,
@@ -1292,49 +1298,42 @@ __global__ __launch_bounds__(256) void batch_eval_kernel(const BatchInst* __rest
   }
 }
 
-cvw_status batch_vertex_pass(int P, const BatchInst* inst, const int2* items, int n_items, const TensorTables* tabs,
-                             int stage, int grid, hipStream_t s) {
-  if (n_items <= 0) return CVW_OK;
-  const dim3 g(std::max(1, std::min(grid, n_items))), b(256);
-  switch (P) {
-    case 1: hipLaunchKernelGGL(batch_vertex_kernel<1>, g, b, 0, s, inst, items, n_items, tabs, stage); break;
-    case 2: hipLaunchKernelGGL(batch_vertex_kernel<2>, g, b, 0, s, inst, items, n_items, tabs, stage); break;
-    case 3: hipLaunchKernelGGL(batch_vertex_kernel<3>, g, b, 0, s, inst, items, n_items, tabs, stage); break;
-    default: set_error("degree not supported on the GPU path"); return CVW_EUNSUPPORTED;
+template <int P>
+__device__ __forceinline__ void batch_eval_flux(const BatchInst* __restrict__ inst, const BatchList& l, int first,
+                                                const TensorTables* __restrict__ tabs, const LaneRec* sl, int stage) {
+  switch (l.flux) {
+    case CVW_ADVECT_CONST: batch_eval_list<P, CVW_ADVECT_CONST>(inst, l, first, tabs[P], sl, stage); break;
+    case CVW_BURGERS: batch_eval_list<P, CVW_BURGERS>(inst, l, first, tabs[P], sl, stage); break;
+    default: batch_eval_list<P, CVW_KPP>(inst, l, first, tabs[P], sl, stage); break;
   }
+}
+
+__global__ __launch_bounds__(256) void batch_eval_kernel(const BatchInst* __restrict__ inst, BatchLists L,
+                                                         const TensorTables* __restrict__ tabs,
+                                                         const LaneRec* __restrict__ lanes, int stage) {
+  __shared__ LaneRec sl[16];
+  int k = 0, first = 0;
+  while (static_cast<int>(blockIdx.x) >= L.l[k].end) first = L.l[k++].end;
+  const BatchList l = L.l[k];
+  load_lane_tables(lanes + 16 * l.P, sl);
+  __syncthreads();
+  switch (l.P) {
+    case 1: batch_eval_flux<1>(inst, l, first, tabs, sl, stage); break;
+    case 2: batch_eval_flux<2>(inst, l, first, tabs, sl, stage); break;
+    default: batch_eval_flux<3>(inst, l, first, tabs, sl, stage); break;
+  }
+}
+
+cvw_status batch_vertex_pass(const BatchInst* inst, const BatchLists& L, int stage, hipStream_t s) {
+  if (L.count == 0) return CVW_OK;
+  hipLaunchKernelGGL(batch_vertex_kernel, dim3(L.l[L.count - 1].end), dim3(256), 0, s, inst, L, stage);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 
-template <int P>
-static void launch_batch_eval(int flux, dim3 g, const BatchInst* inst, const int2* items, int n_items,
-                              const TensorTables* tabs, const LaneRec* lanes, int stage, hipStream_t s) {
-  const dim3 b(256);
-  switch (flux) {
-    case CVW_ADVECT_CONST:
-      hipLaunchKernelGGL((batch_eval_kernel<P, CVW_ADVECT_CONST>), g, b, 0, s, inst, items, n_items, tabs, lanes, stage);
-      break;
-    case CVW_BURGERS:
-      hipLaunchKernelGGL((batch_eval_kernel<P, CVW_BURGERS>), g, b, 0, s, inst, items, n_items, tabs, lanes, stage);
-      break;
-    default:
-      hipLaunchKernelGGL((batch_eval_kernel<P, CVW_KPP>), g, b, 0, s, inst, items, n_items, tabs, lanes, stage);
-      break;
-  }
-}
-
-cvw_status batch_eval_pass(int P, int flux, const BatchInst* inst, const int2* items, int n_items,
-                           const TensorTables* tabs, const LaneRec* lanes, int stage, int grid, hipStream_t s) {
-  if (n_items <= 0) return CVW_OK;
-  if (flux != CVW_ADVECT_CONST && flux != CVW_BURGERS && flux != CVW_KPP) {
-    set_error("batched stages: scalar fluxes on DG quadrilaterals"); return CVW_EUNSUPPORTED;
-  }
-  const dim3 g(std::max(1, std::min(grid, n_items)));
-  switch (P) {
-    case 1: launch_batch_eval<1>(flux, g, inst, items, n_items, tabs, lanes, stage, s); break;
-    case 2: launch_batch_eval<2>(flux, g, inst, items, n_items, tabs, lanes, stage, s); break;
-    case 3: launch_batch_eval<3>(flux, g, inst, items, n_items, tabs, lanes, stage, s); break;
-    default: set_error("degree not supported on the GPU path"); return CVW_EUNSUPPORTED;
-  }
+cvw_status batch_eval_pass(const BatchInst* inst, const BatchLists& L, const TensorTables* tabs,
+                           const LaneRec* lanes, int stage, hipStream_t s) {
+  if (L.count == 0) return CVW_OK;
+  hipLaunchKernelGGL(batch_eval_kernel, dim3(L.l[L.count - 1].end), dim3(256), 0, s, inst, L, tabs, lanes, stage);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 

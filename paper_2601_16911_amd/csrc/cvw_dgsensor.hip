@@ -510,15 +510,28 @@ __global__ __launch_bounds__(256, 4) void dgq_sensor_tile_kernel(const float* __
 }
 
 // Batched stages: the fused pass over the (instance, tile) items of every
-// instance of degree P, a fixed stride walk; each tile runs the single-mesh
-// body, so gamma is bitwise that of the single-mesh pass.
+// list; each tile runs the single-mesh body, so gamma is bitwise that of the
+// single-mesh pass.
 template <int P>
-__global__ __launch_bounds__(256, 4) void batch_sensor_kernel(const BatchInst* __restrict__ inst,
-                                                           const int2* __restrict__ items, int n_items, int stage) {
-  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-    const int2 w = items[it];
+__device__ __forceinline__ void batch_sensor_list(const BatchInst* __restrict__ inst, const BatchList& l, int first,
+                                                  int stage) {
+  const BatchRun r = batch_run(l, first);
+  for (int it = r.lo; it < r.hi; ++it) {
+    const int2 w = l.items[it];
     const BatchInst& I = inst[w.x];
     sensor_tile_body<P>(I.u_in[stage], I.gam, I.sa, I.ms, w.y, TILE_ALL, nullptr, nullptr, nullptr);
+  }
+}
+
+__global__ __launch_bounds__(256, 4) void batch_sensor_kernel(const BatchInst* __restrict__ inst, BatchLists L,
+                                                              int stage) {
+  int k = 0, first = 0;
+  while (static_cast<int>(blockIdx.x) >= L.l[k].end) first = L.l[k++].end;
+  const BatchList l = L.l[k];
+  switch (l.P) {
+    case 1: batch_sensor_list<1>(inst, l, first, stage); break;
+    case 2: batch_sensor_list<2>(inst, l, first, stage); break;
+    default: batch_sensor_list<3>(inst, l, first, stage); break;
   }
 }
 
@@ -616,16 +629,9 @@ cvw_status dgquad_sensor_tile(const cvw_mesh* m, const cvw_params* prm, const fl
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 
-cvw_status batch_sensor_pass(int P, const BatchInst* inst, const int2* items, int n_items, int stage, int grid,
-                             hipStream_t s) {
-  if (n_items <= 0) return CVW_OK;
-  const dim3 g(std::max(1, std::min(grid, n_items))), b(256);
-  switch (P) {
-    case 1: hipLaunchKernelGGL(batch_sensor_kernel<1>, g, b, 0, s, inst, items, n_items, stage); break;
-    case 2: hipLaunchKernelGGL(batch_sensor_kernel<2>, g, b, 0, s, inst, items, n_items, stage); break;
-    case 3: hipLaunchKernelGGL(batch_sensor_kernel<3>, g, b, 0, s, inst, items, n_items, stage); break;
-    default: set_error("degree not supported on the GPU path"); return CVW_EUNSUPPORTED;
-  }
+cvw_status batch_sensor_pass(const BatchInst* inst, const BatchLists& L, int stage, hipStream_t s) {
+  if (L.count == 0) return CVW_OK;
+  hipLaunchKernelGGL(batch_sensor_kernel, dim3(L.l[L.count - 1].end), dim3(256), 0, s, inst, L, stage);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 

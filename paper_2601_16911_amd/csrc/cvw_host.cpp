@@ -2720,7 +2720,7 @@ struct cvw_batch {
   int n = 0;
   int device = 0;
   int external = 0;                               // device arrays in a caller buffer (cvw_batch_build_in)
-  int grid = 0;                                   // blocks per launch (<= 0: one per item)
+  int grid = 0;                                   // blocks per work list (<= 0: BATCH_BLOCKS over the pass)
   std::vector<const cvw_mesh*> meshes;
   std::vector<cvw_params> prms;
   std::vector<void*> u;
@@ -2729,7 +2729,8 @@ struct cvw_batch {
   size_t ws_bytes = 0;
   // work lists: fused sensor pass and vertex pass per degree, cell pass per (degree, flux)
   struct List { int P = 0, flux = 0, n = 0; int2* d = nullptr; };
-  std::vector<List> slists, vlists, elists;
+  using Lists = std::vector<List>;
+  Lists slists, vlists, elists;
   cvw::BatchInst* d_inst = nullptr;
   cvw::TensorTables* d_tabs = nullptr;            // [4], index = degree
   cvw::LaneRec* d_lanes = nullptr;                // [4][16]
@@ -2761,23 +2762,38 @@ static void batch_free(cvw_batch* b) {
   delete b;
 }
 
+// The lists of a pass with their share of the launch's blocks.  By default one
+// run length for the whole pass, chosen for at most BATCH_BLOCKS blocks: a few
+// resident rounds (a step of 24 meshes: 2048 blocks 342 us, 4096 308, 8192 310,
+// one item per block 359).
+constexpr int64_t BATCH_BLOCKS = 4096;
+static BatchLists batch_lists(const cvw_batch* b, const cvw_batch::Lists& lists) {
+  static_assert(MAXP * 3 <= BatchLists::MAX, "a list per degree and scalar flux");
+  BatchLists L;
+  int64_t items = 0;
+  for (const auto& l : lists) items += l.n;
+  const int run = static_cast<int>((items + BATCH_BLOCKS - 1) / BATCH_BLOCKS);
+  int end = 0;
+  for (const auto& l : lists) {
+    BatchList& o = L.l[L.count++];
+    o.items = l.d;
+    o.n = l.n;
+    o.run = b->grid > 0 ? (l.n - 1) / std::min(b->grid, l.n) + 1 : run;
+    end += ((l.n - 1) / o.run + 8) / 8 * 8;
+    o.end = end;
+    o.P = l.P;
+    o.flux = l.flux;
+  }
+  return L;
+}
+
 // one pass of every stage kernel on stream s (used eagerly and under capture)
 static cvw_status batch_launch_stage(const cvw_batch* b, int stage, hipStream_t s) {
-  for (const auto& l : b->slists) {
-    const cvw_status st = batch_sensor_pass(l.P, b->d_inst, l.d, l.n, stage, b->grid > 0 ? b->grid : l.n, s);
-    if (st != CVW_OK) return st;
-  }
-  for (const auto& l : b->vlists) {
-    const cvw_status st = batch_vertex_pass(l.P, b->d_inst, l.d, l.n, b->d_tabs, stage,
-                                            b->grid > 0 ? b->grid : l.n, s);
-    if (st != CVW_OK) return st;
-  }
-  for (const auto& l : b->elists) {
-    const cvw_status st = batch_eval_pass(l.P, l.flux, b->d_inst, l.d, l.n, b->d_tabs, b->d_lanes, stage,
-                                          b->grid > 0 ? b->grid : l.n, s);
-    if (st != CVW_OK) return st;
-  }
-  return CVW_OK;
+  cvw_status st = batch_sensor_pass(b->d_inst, batch_lists(b, b->slists), stage, s);
+  if (st == CVW_OK) st = batch_vertex_pass(b->d_inst, batch_lists(b, b->vlists), stage, s);
+  if (st == CVW_OK)
+    st = batch_eval_pass(b->d_inst, batch_lists(b, b->elists), b->d_tabs, b->d_lanes, stage, s);
+  return st;
 }
 
 static cvw_status batch_upload_descriptors(cvw_batch* b, void* ws) {

@@ -478,19 +478,33 @@ cvw_status seghp_candidates(const cvw_mesh* m, const cvw_params* prm, const doub
 cvw_status seghp_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const double* u, const double* cand,
                       double* rcell, double* R, double* gamma, double* alpha, uint32_t* status, hipStream_t s,
                       const LineStage& lst);
-// batched fused sensor pass over (instance, tile) items of degree P
-// (cvw_dgsensor.hip), and the tile arguments of a mesh
-cvw_status batch_sensor_pass(int P, const BatchInst* inst, const int2* items, int n_items, int stage, int grid,
-                             hipStream_t s);
+// Batched DG quadrilateral stage over many meshes.  A pass holds up to 9 work
+// lists, one per degree (cell pass: per degree and flux), of (instance,
+// logical block) items; it is ONE launch, list k taken by the blocks
+// [l[k - 1].end, l[k].end), each walking a run of consecutive items (the
+// blocks of one XCD hold consecutive runs: neighbour rows share its L2).
+// Few of the lists fill the chip by themselves: a step of 16 meshes, 27
+// launches one after another, took 270 us; as 6 launches with one item per
+// block 221 us; with runs (the lane tables are staged once per block) 189 us.
+struct BatchList {
+  const int2* items = nullptr;
+  int n = 0;       // items
+  int run = 1;     // items per block
+  int end = 0;     // blocks of the lists up to this one (each list a multiple of 8)
+  int P = 0, flux = 0;
+};
+struct BatchLists {
+  static constexpr int MAX = 9;
+  BatchList l[MAX];
+  int count = 0;
+};
+// fused sensor pass (cvw_dgsensor.hip), and the tile arguments of a mesh
+cvw_status batch_sensor_pass(const BatchInst* inst, const BatchLists& L, int stage, hipStream_t s);
 SensorTileArgs make_sensor_tile_args(const cvw_mesh* m);
-// batched DG quadrilateral stage over many meshes (cvw_dgquad.hip): the
-// vertex pass is launched once per degree P, the cell pass once per (P, flux);
-// items are (instance, logical block) pairs of the instances of that class,
-// processed by a grid-stride loop
-cvw_status batch_vertex_pass(int P, const BatchInst* inst, const int2* items, int n_items, const TensorTables* tabs,
-                             int stage, int grid, hipStream_t s);
-cvw_status batch_eval_pass(int P, int flux, const BatchInst* inst, const int2* items, int n_items,
-                           const TensorTables* tabs, const LaneRec* lanes, int stage, int grid, hipStream_t s);
+// vertex pass and cell pass (cvw_dgquad.hip)
+cvw_status batch_vertex_pass(const BatchInst* inst, const BatchLists& L, int stage, hipStream_t s);
+cvw_status batch_eval_pass(const BatchInst* inst, const BatchLists& L, const TensorTables* tabs,
+                           const LaneRec* lanes, int stage, hipStream_t s);
 // learned-sensor network (cvw_mlp.hip)
 cvw_status mlp_infer(const MlpDev& W, const uint16_t* feat, int64_t n, float* gamma, hipStream_t s,
                      const MlpGuard* guard = nullptr);
