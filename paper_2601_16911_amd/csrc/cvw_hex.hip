@@ -9,7 +9,8 @@
 //  * hex_sensor_kernel -- one thread per cell: the cell-vertex WENO sensor
 //    (eq. finalweno, eq. gamma).
 //  * hex_eval_kernel -- a team of lanes per cell, one lane per node (8 lanes
-//    for Q_1, 27 of 32 for Q_2): the viscosity (eq. lostab), the
+//    for Q_1, 27 of 32 for Q_2), or, on large Q_2 meshes, hex_plane_kernel --
+//    a quad of lanes per cell, a lane per plane of nodes: the viscosity (eq. lostab), the
 //    shock-capturing weights (eqs. dissrateorig to alphaq), the volume and
 //    interface terms of the DG residual in float32, and optionally the
 //    Runge-Kutta stage update with the exact (diagonal, Gauss-collocated)
@@ -711,6 +712,344 @@ __global__ __launch_bounds__(256) void hex_eval_kernel(const float* __restrict__
   if (__ballot(nonfinite) && (threadIdx.x & 63) == 0) atomicOr(status, ST_NONFINITE);
 }
 
+// Contractions across the planes of a quad (lanes 0..2 of four): three values
+// at a time, the DPP source fused into the multiply-add; the s_nop gives the
+// wait states a DPP read of a just written register needs.
+// r_i += sum_j c[j] x_i(lane j)
+__device__ __forceinline__ void qfma3(float& r0, float& r1, float& r2, float x0, float x1, float x2,
+                                      const float (&c)[3]) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %3, %6 quad_perm:[0,0,0,0]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %1, %4, %6 quad_perm:[0,0,0,0]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %2, %5, %6 quad_perm:[0,0,0,0]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %0, %3, %7 quad_perm:[1,1,1,1]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %1, %4, %7 quad_perm:[1,1,1,1]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %2, %5, %7 quad_perm:[1,1,1,1]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %0, %3, %8 quad_perm:[2,2,2,2]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %1, %4, %8 quad_perm:[2,2,2,2]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %2, %5, %8 quad_perm:[2,2,2,2]" CVW_DPP_TAIL
+      : "+&v"(r0), "+&v"(r1), "+&v"(r2)
+      : "v"(x0), "v"(x1), "v"(x2), "v"(c[0]), "v"(c[1]), "v"(c[2]));
+}
+// r_q += c x(lane q)
+__device__ __forceinline__ void qspread3(float& r0, float& r1, float& r2, float x, float c) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %3, %4 quad_perm:[0,0,0,0]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %1, %3, %4 quad_perm:[1,1,1,1]" CVW_DPP_TAIL "\n\t"
+      "v_fmac_f32_dpp %2, %3, %4 quad_perm:[2,2,2,2]" CVW_DPP_TAIL
+      : "+&v"(r0), "+&v"(r1), "+&v"(r2)
+      : "v"(x), "v"(c));
+}
+
+// Q_2 cell pass, a quad of lanes per cell (16 cells per wavefront): lane c < 3
+// holds the nine nodes (a, b) of plane c, lane 3 mirrors plane 2 and stores
+// nothing.  Contractions along x and y stay in the lane's registers, those
+// along z read the other lanes of the quad (DPP); no LDS.  x and y faces: lane
+// c evaluates the three points of plane c; z faces: the three points (p, q = c),
+// with the nodes of the cell and its neighbour on those lines read from memory
+// in that order.  Bound by VALU issue (5300 instructions per wavefront, two
+// wavefronts per SIMD at 225 registers; three would spill).  201,666 cells,
+// Euler: 138 us against 371 with a lane per node and LDS exchange, which
+// waits on 47 loads and 150 LDS operations per two cells.
+template <int FLUX>
+__global__ __launch_bounds__(64) void hex_plane_kernel(const float* __restrict__ u, const float* __restrict__ u0,
+                                                       float* __restrict__ out, float* __restrict__ gamma_out,
+                                                       float* __restrict__ alpha_out,
+                                                       const float* __restrict__ gamma_in,
+                                                       const int32_t* __restrict__ nbr,
+                                                       const HexTables* __restrict__ tab, int64_t E, int64_t nb,
+                                                       MethodScalars ms, int mode, float dt, float a0, float b0,
+                                                       uint32_t* __restrict__ status) {
+  constexpr int N1 = 3, NN = 9, NL = 27, NV = HexNV<FLUX>::value;
+  const int64_t e0 = xcd_block(blockIdx.x, nb) * 16;
+  if (e0 >= E) return;
+  const int64_t e = e0 + (threadIdx.x >> 2);
+  const int tl = threadIdx.x & 3, tc = tl < 2 ? tl : 2;
+  const int64_t ec = e < E ? e : E - 1;
+  const bool on = e < E && tl < 3;
+  // the nine values of plane c of a cell
+  auto plane = [&](const float* p, int64_t cell, int v, float (&x)[NN]) {
+    const float* q = p + (v * E + cell) * NL + NN * tc;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) x[i] = q[i];
+  };
+  // the nine values with second index c: x[p + 3 m] is node (p, c, m)
+  auto lines = [&](const float* p, int64_t cell, int v, float (&x)[NN]) {
+    const float* q = p + (v * E + cell) * NL + N1 * tc;
+#pragma unroll
+    for (int m = 0; m < N1; ++m)
+#pragma unroll
+      for (int i = 0; i < N1; ++i) x[i + N1 * m] = q[i + NN * m];
+  };
+  float uv[NV][NN];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) plane(u, ec, v, uv[v]);
+  int32_t id[6];
+#pragma unroll
+  for (int f = 0; f < 6; ++f) id[f] = nbr[ec * 6 + f];
+  const float gam = ms.sensor_kind != CVW_SENSOR_FIXED ? gamma_in[ec] : ms.fixed_gamma;
+  float dz[N1], dzc[N1];
+#pragma unroll
+  for (int j = 0; j < N1; ++j) {
+    dz[j] = tab->D1[tc][j];
+    dzc[j] = tab->D1[j][tc];
+  }
+  const float wz = tab->w1[tc];
+  float Wab[NN];                                       // in-plane weights (uniform)
+#pragma unroll
+  for (int i = 0; i < NN; ++i) Wab[i] = tab->w1[i % N1] * tab->w1[i / N1];
+  const float Wc = wz * tab->W0;
+
+  // in-plane derivatives along x and y, and along z across the quad
+  auto ddx = [&](const float (&x)[NN], int i) {
+    const int a = i % N1, b = i / N1;
+    float s = tab->D1[a][0] * x[N1 * b];
+    s = fmaf(tab->D1[a][1], x[N1 * b + 1], s);
+    return fmaf(tab->D1[a][2], x[N1 * b + 2], s);
+  };
+  auto ddy = [&](const float (&x)[NN], int i) {
+    const int a = i % N1, b = i / N1;
+    float s = tab->D1[b][0] * x[a];
+    s = fmaf(tab->D1[b][1], x[a + N1], s);
+    return fmaf(tab->D1[b][2], x[a + 2 * N1], s);
+  };
+  auto ddz = [&](const float (&x)[NN], const float (&c)[N1], float (&g)[NN]) {
+#pragma unroll
+    for (int i = 0; i < NN; ++i) g[i] = 0.0f;
+#pragma unroll
+    for (int b = 0; b < N1; ++b)
+      qfma3(g[N1 * b], g[N1 * b + 1], g[N1 * b + 2], x[N1 * b], x[N1 * b + 1], x[N1 * b + 2], c);
+  };
+
+  // ---- viscosity (eq. lostab)
+  float lam = ms.lam_g;
+  if (!(lam > 0.0f)) {
+    lam = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) {
+      float un[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) un[v] = uv[v][i];
+      lam = fmaxf(lam, hex_speed_all<FLUX>(ms, un));
+    }
+    lam = quad_max(lam);
+  }
+  // ---- shock-capturing weights of the sensor field (cells with gamma_e < C_gamma)
+  float gs[NN];                                        // nu alpha (1 - gamma) at the nodes
+#pragma unroll
+  for (int i = 0; i < NN; ++i) gs[i] = 1.0f;
+  if (ms.sc_on && gam < ms.c_gamma) {
+    float gx[NN], gy[NN], gz[NN], h[NN], d2z[N1];
+#pragma unroll
+    for (int j = 0; j < N1; ++j) d2z[j] = tab->D2[tc][j];
+    ddz(uv[0], dz, gz);
+    ddz(uv[0], d2z, h);
+    float Sv = 0.0f, Tv = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) {
+      gx[i] = ddx(uv[0], i);
+      gy[i] = ddy(uv[0], i);
+    }
+#pragma unroll
+    for (int i = 0; i < NN; ++i) {
+      const int a = i % N1, b = i / N1;
+      float a2 = tab->wa[0] * gx[i] * gx[i] + tab->wa[1] * gy[i] * gy[i] + tab->wa[2] * gz[i] * gz[i];
+      float xx = 0.0f, yy = 0.0f;
+#pragma unroll
+      for (int j = 0; j < N1; ++j) {
+        xx = fmaf(tab->D2[a][j], uv[0][j + N1 * b], xx);
+        yy = fmaf(tab->D2[b][j], uv[0][a + N1 * j], yy);
+      }
+      const float xy = ddy(gx, i), xz = ddx(gz, i), yz = ddy(gz, i);
+      // multi-index order (2,0,0), (1,1,0), (1,0,1), (0,2,0), (0,1,1), (0,0,2)
+      a2 = fmaf(tab->wa[3] * xx, xx, a2);
+      a2 = fmaf(tab->wa[4] * xy, xy, a2);
+      a2 = fmaf(tab->wa[5] * xz, xz, a2);
+      a2 = fmaf(tab->wa[6] * yy, yy, a2);
+      a2 = fmaf(tab->wa[7] * yz, yz, a2);
+      a2 = fmaf(tab->wa[8] * h[i], h[i], a2);
+      const float at = fsqrt(a2);
+      const float px = gx[i] * tab->sc[0], py = gy[i] * tab->sc[1], pz = gz[i] * tab->sc[2];
+      const float f = (1.0f - gam) * (px * px + py * py + pz * pz);
+      const float W = Wab[i] * Wc;
+      Sv = fmaf(W, f, Sv);
+      Tv = fmaf(W * at, f, Tv);
+      gs[i] = at;
+    }
+    Sv = quad_sum(tl < 3 ? Sv : 0.0f);
+    Tv = quad_sum(tl < 3 ? Tv : 0.0f);
+    const bool act = Sv > 0.0f && Tv > 0.0f;
+    const float q = Sv / Tv;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) gs[i] = act ? gs[i] * q : 1.0f;
+  }
+  if (mode == MODE_SENSOR) {
+    if (on && tl == 0 && gamma_out) gamma_out[e] = gam;
+    if (on && alpha_out)
+#pragma unroll
+      for (int i = 0; i < NN; ++i) alpha_out[e * NL + NN * tc + i] = gs[i];
+    return;
+  }
+  const float nug = lam * tab->nuf * (1.0f - gam);
+#pragma unroll
+  for (int i = 0; i < NN; ++i) gs[i] *= nug;
+
+  // ---- volume terms: -grad phi_j . f(u) + nu alpha (1 - gamma) grad phi_j . grad u
+  float iv[NN], pr[NN];                                // 1 / rho and pressure (Euler)
+#pragma unroll
+  for (int i = 0; i < NN; ++i) {
+    iv[i] = pr[i] = 0.0f;
+    if constexpr (FLUX == CVW_EULER) {
+      iv[i] = frcp(uv[0][i]);
+      const float m2 = uv[1][i] * uv[1][i] + uv[2][i] * uv[2][i] + uv[3][i] * uv[3][i];
+      pr[i] = (ms.fp[0] - 1.0f) * (uv[4][i] - 0.5f * m2 * iv[i]);
+    }
+  }
+  float r[NV][NN];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    float g[NN], F[NN];
+    auto fluxd = [&](int i, int d) {                   // f_d of variable v
+      if constexpr (FLUX == CVW_EULER) {
+        const float md = uv[1 + d][i];
+        if (v == 0) return md;
+        const float vd = md * iv[i];
+        return v < 4 ? uv[v][i] * vd + (v - 1 == d ? pr[i] : 0.0f) : (uv[4][i] + pr[i]) * vd;
+      } else {
+        return hex_flux<FLUX>(ms, uv[0][i], d);
+      }
+    };
+    ddz(uv[v], dz, g);
+    const float kz = Wc * tab->sc[2], kx = Wc * tab->sc[0], ky = Wc * tab->sc[1];
+#pragma unroll
+    for (int i = 0; i < NN; ++i) F[i] = Wab[i] * kz * (gs[i] * (g[i] * tab->sc[2]) - fluxd(i, 2));
+    ddz(F, dzc, r[v]);
+#pragma unroll
+    for (int i = 0; i < NN; ++i) F[i] = Wab[i] * kx * (gs[i] * (ddx(uv[v], i) * tab->sc[0]) - fluxd(i, 0));
+#pragma unroll
+    for (int i = 0; i < NN; ++i)
+#pragma unroll
+      for (int q = 0; q < N1; ++q) r[v][i] = fmaf(tab->D1[q][i % N1], F[q + N1 * (i / N1)], r[v][i]);
+#pragma unroll
+    for (int i = 0; i < NN; ++i) F[i] = Wab[i] * ky * (gs[i] * (ddy(uv[v], i) * tab->sc[1]) - fluxd(i, 1));
+#pragma unroll
+    for (int i = 0; i < NN; ++i)
+#pragma unroll
+      for (int q = 0; q < N1; ++q) r[v][i] = fmaf(tab->D1[q][i / N1], F[i % N1 + N1 * q], r[v][i]);
+  }
+
+  // ---- interface terms: face f = 2 d + s, the neighbour read through its face f ^ 1
+  float pn[NV][NN];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) plane(u, id[0], v, pn[v]);
+#pragma unroll
+  for (int f = 0; f < 4; ++f) {
+    const int d = f >> 1, s = f & 1, sp = d ? N1 : 1, sq = d ? 1 : N1;   // strides along and across the normal
+    float up[N1][NV];
+#pragma unroll
+    for (int q = 0; q < N1; ++q)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        float x = tab->Lend[1 - s][0] * pn[v][sq * q];
+        x = fmaf(tab->Lend[1 - s][1], pn[v][sq * q + sp], x);
+        up[q][v] = fmaf(tab->Lend[1 - s][2], pn[v][sq * q + 2 * sp], x);
+      }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      if (f < 3) plane(u, id[f + 1], v, pn[v]);
+      else lines(u, id[4], v, pn[v]);
+    }
+#pragma unroll
+    for (int q = 0; q < N1; ++q) {
+      float um[NV], fs[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        float x = tab->Lend[s][0] * uv[v][sq * q];
+        x = fmaf(tab->Lend[s][1], uv[v][sq * q + sp], x);
+        um[v] = fmaf(tab->Lend[s][2], uv[v][sq * q + 2 * sp], x);
+      }
+      hex_num_flux<FLUX>(ms, um, up[q], d, s ? 1.0f : -1.0f, fs);
+      const float wq = tab->w1[q] * tab->Jf[d] * wz;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const float fw = wq * fs[v];
+#pragma unroll
+        for (int m = 0; m < N1; ++m) r[v][sq * q + sp * m] = fmaf(tab->Lend[s][m], fw, r[v][sq * q + sp * m]);
+      }
+    }
+  }
+  {
+    // z faces: the own lines give both traces
+    float um[2][N1][NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      float x[NN];
+      lines(u, ec, v, x);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int p = 0; p < N1; ++p)
+          um[s][p][v] = fmaf(tab->Lend[s][2], x[p + 2 * N1],
+                             fmaf(tab->Lend[s][1], x[p + N1], tab->Lend[s][0] * x[p]));
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const float le = tab->Lend[s][tc];
+      float up[N1][NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int p = 0; p < N1; ++p)
+          up[p][v] = fmaf(tab->Lend[1 - s][2], pn[v][p + 2 * N1],
+                          fmaf(tab->Lend[1 - s][1], pn[v][p + N1], tab->Lend[1 - s][0] * pn[v][p]));
+      if (s == 0)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) lines(u, id[5], v, pn[v]);
+#pragma unroll
+      for (int p = 0; p < N1; ++p) {
+        float fs[NV];
+        hex_num_flux<FLUX>(ms, um[s][p], up[p], 2, s ? 1.0f : -1.0f, fs);
+        const float wq = tab->w1[p] * tab->Jf[2] * wz;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) qspread3(r[v][p], r[v][p + N1], r[v][p + 2 * N1], wq * fs[v], le);
+      }
+    }
+  }
+
+  // ---- output
+  bool nonfinite = false;
+  if (on) {
+    const float iWc = 1.0f / Wc;
+    float iw1[N1];
+#pragma unroll
+    for (int j = 0; j < N1; ++j) iw1[j] = 1.0f / tab->w1[j];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const int64_t idx = (v * E + e) * NL + NN * tc;
+      float o[NN];
+#pragma unroll
+      for (int i = 0; i < NN; ++i) o[i] = r[v][i];
+      if (mode != MODE_RESIDUAL) {
+        float base[NN];
+#pragma unroll
+        for (int i = 0; i < NN; ++i) base[i] = 0.0f;
+        if (a0 != 0.0f)
+#pragma unroll
+          for (int i = 0; i < NN; ++i) base[i] = a0 * u0[idx + i];
+#pragma unroll
+        for (int i = 0; i < NN; ++i) o[i] = base[i] + b0 * (uv[v][i] - dt * o[i] * (iWc * (iw1[i % N1] * iw1[i / N1])));
+      }
+#pragma unroll
+      for (int i = 0; i < NN; ++i) {
+        nonfinite = nonfinite || !isfinite(o[i]);
+        out[idx + i] = o[i];
+      }
+    }
+    if (tl == 0 && gamma_out) gamma_out[e] = gam;
+  }
+  if (__ballot(nonfinite) && threadIdx.x == 0) atomicOr(status, ST_NONFINITE);
+}
+
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
@@ -727,6 +1066,11 @@ cvw_status hex_candidates(const cvw_mesh* m, const cvw_params* prm, const float*
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 
+// From this many Q_2 cells on the quad-per-cell pass: it has an eighth of the
+// wavefronts, each eight times as long.  Step, Euler, lane per node against
+// quad per cell: 12^3 cells 94 and 106 us, 16^3 106 and 117, 24^3 183 and 129,
+// 32^3 283 and 215 (advection: 81 and 82, 106 and 95, 133 and 100 from 16^3).
+constexpr int64_t HEX_PLANE_CELLS = 6144;
 template <int P, int FLUX>
 static void launch_hex_eval(const cvw_mesh* m, const MethodScalars& ms, int mode, const float* u, const float* u0,
                             float* out, float* gamma, float* alpha, const float* cand, float* gbuf, uint32_t* status,
@@ -741,6 +1085,14 @@ static void launch_hex_eval(const cvw_mesh* m, const MethodScalars& ms, int mode
                        m->d_hext, m->E, ms);
   // gamma_e is already in the caller's array when the sensor pass wrote it there
   float* gout = (ms.sensor_kind != CVW_SENSOR_FIXED && gamma) ? nullptr : gamma;
+  if constexpr (P == 2) {
+    if (m->E >= HEX_PLANE_CELLS) {
+      const int64_t nb = ((m->E + 15) / 16 + 7) / 8 * 8;
+      hipLaunchKernelGGL((hex_plane_kernel<FLUX>), dim3(static_cast<unsigned>(nb)), dim3(64), 0, s, u, u0, out, gout,
+                         alpha, g, m->d_nbr, m->d_hext, m->E, nb, ms, mode, dt, a0, b0, status);
+      return;
+    }
+  }
   hipLaunchKernelGGL((hex_eval_kernel<P, FLUX>), dim3(grid), dim3(256), 0, s, u, u0, out, gout, alpha, g, m->d_nbr,
                      m->d_hext, m->E, nblk, ms, mode, dt, a0, b0, status);
 }
