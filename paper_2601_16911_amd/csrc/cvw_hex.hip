@@ -363,7 +363,16 @@ __global__ __launch_bounds__(256) void hex_sensor_kernel(const float* __restrict
   __shared__ float su[256 * NL];
   const int64_t base = static_cast<int64_t>(blockIdx.x) * 256;
   const int64_t ncell = E - base < 256 ? E - base : 256;
-  for (int64_t i = threadIdx.x; i < ncell * NL; i += 256) su[i] = u[base * NL + i];
+  {
+    // clamped, all loads in flight before the LDS stores
+    const float* ub = u + base * NL;
+    const int last = static_cast<int>(ncell) * NL - 1;
+    float x[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) x[j] = ub[min(static_cast<int>(threadIdx.x) + 256 * j, last)];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) su[threadIdx.x + 256 * j] = x[j];
+  }
   __syncthreads();
   if (threadIdx.x >= ncell) return;
   const int64_t e = base + threadIdx.x;
