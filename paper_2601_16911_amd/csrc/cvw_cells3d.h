@@ -43,6 +43,7 @@ struct HexTables {
 constexpr int TET_MAXP = 2;
 constexpr int TET_NLOC = (TET_MAXP + 1) * (TET_MAXP + 2) * (TET_MAXP + 3) / 6;
 constexpr int TET_NK = TET_NLOC - 1, TET_NQ = (TET_MAXP + 1) * (TET_MAXP + 1) * (TET_MAXP + 1), TET_NFP = 7;
+constexpr int TET_NLINE = (TET_MAXP + 1) * (TET_MAXP + 1), TET_NFN = (TET_MAXP + 1) * (TET_MAXP + 2) / 2;
 struct TetTables {
   int p, nloc, nk, nq;
   double B[TET_NQ][TET_NLOC];            // phi_j at the volume points
@@ -50,13 +51,13 @@ struct TetTables {
   double H2[6][TET_NLOC];                // second reference derivatives (xx, xy, xz, yy, yz, zz; constant for p <= 2)
   double Gc[3][TET_NLOC];                // d phi_j / d xi_b at the centroid (1/4, 1/4, 1/4)
   double xq[TET_NQ][3], wq[TET_NQ];      // volume points and weights (the weights sum to 1/6)
-  float Bs[TET_NQ][TET_NLOC];            // float32 copies for the residual: phi_j, d phi_j / d xi_b, weights
-  float Gs[3][TET_NQ][TET_NLOC];
-  float wqs[TET_NQ];
+  // the volume points as lines along x, relative to the centroid: y, z, y / 2,
+  // z / 2, then of the line's (up to three) points x, x / 2, the weight w, w x
+  float line[TET_NLINE][16];
   double TV[4][TET_NK][TET_NLOC];        // reference derivatives D^m phi_j at reference vertex l, 1 <= |m| <= p
-  float Bf[4][TET_NFP][TET_NLOC];        // phi_j at the points of face f
+  float Bt[TET_NFP][TET_NFN];            // the face's nodes (vertices a < b < c, then midpoints ab, ac, bc) at its points
   float wf[TET_NFP];                     // face weights (sum 1/2)
-  int8_t perm[6][TET_NFP];               // the rule point a point becomes under a permutation of the face's vertices
+  uint32_t fmap[32];                     // face f2, vertex permutation s: 4 bits per node of the own face, the neighbour's node there (8 f2 + s)
   float Minv[TET_NLOC][TET_NLOC];        // inverse reference mass matrix
   int8_t kk[TET_NK][3];                  // the multi-indices
 };

@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(64) void hex_plane_kernel(const float* __restrict__
       }
 #pragma unroll
       for (int i = 0; i < NN; ++i) {
-        nonfinite = nonfinite || !isfinite(o[i]);
+        nonfinite |= !isfinite(o[i]);
         out[idx + i] = o[i];
       }
     }

@@ -858,10 +858,19 @@ static void fill_tet_tables(TetTables& T, int p) {
       T.G[0][qq][j] = der(j, 1, 0, 0, x, y, z);
       T.G[1][qq][j] = der(j, 0, 1, 0, x, y, z);
       T.G[2][qq][j] = der(j, 0, 0, 1, x, y, z);
-      T.Bs[qq][j] = static_cast<float>(T.B[qq][j]);
-      for (int b = 0; b < 3; ++b) T.Gs[b][qq][j] = static_cast<float>(T.G[b][qq][j]);
     }
-  for (int qq = 0; qq < q; ++qq) T.wqs[qq] = static_cast<float>(T.wq[qq]);
+  for (int qq = 0; qq < q; ++qq) {
+    float* l = T.line[qq / n1];
+    const double x = T.xq[qq][0] - 0.25, y = T.xq[qq][1] - 0.25, z = T.xq[qq][2] - 0.25;
+    l[0] = static_cast<float>(y);
+    l[1] = static_cast<float>(z);
+    l[2] = static_cast<float>(0.5 * y);
+    l[3] = static_cast<float>(0.5 * z);
+    l[4 + qq % n1] = static_cast<float>(x);
+    l[7 + qq % n1] = static_cast<float>(0.5 * x);
+    l[10 + qq % n1] = static_cast<float>(T.wq[qq]);
+    l[13 + qq % n1] = static_cast<float>(T.wq[qq] * x);
+  }
   static const int H[6][3] = {{2, 0, 0}, {1, 1, 0}, {1, 0, 1}, {0, 2, 0}, {0, 1, 1}, {0, 0, 2}};
   for (int h = 0; h < 6; ++h)
     for (int j = 0; j < n; ++j) T.H2[h][j] = der(j, H[h][0], H[h][1], H[h][2], 0.25, 0.25, 0.25);
@@ -903,26 +912,35 @@ static void fill_tet_tables(TetTables& T, int p) {
     }
   }
   for (int g = 0; g < TET_NFP; ++g) T.wf[g] = static_cast<float>(0.5 * wr[g]);
-  static const int FV[4][3] = {{1, 2, 3}, {0, 2, 3}, {0, 1, 3}, {0, 1, 2}};
-  for (int f = 0; f < 4; ++f)
-    for (int g = 0; g < TET_NFP; ++g) {
-      double x[3] = {0, 0, 0};
-      for (int i = 0; i < 3; ++i)
-        for (int d = 0; d < 3; ++d) x[d] += bary[g][i] * RV[FV[f][i]][d];
-      for (int j = 0; j < n; ++j) T.Bf[f][g][j] = static_cast<float>(der(j, 0, 0, 0, x[0], x[1], x[2]));
+  // traces on a face: its vertices a < b < c, for p = 2 then the midpoints ab, ac, bc
+  static const int EA[3] = {0, 0, 1}, EB[3] = {1, 2, 2};
+  for (int g = 0; g < TET_NFP; ++g)
+    for (int i = 0; i < 3; ++i) {
+      const double l = bary[g][i];
+      T.Bt[g][i] = static_cast<float>(p == 1 ? l : l * (2.0 * l - 1.0));
+      if (p == 2) T.Bt[g][3 + i] = static_cast<float>(4.0 * bary[g][EA[i]] * bary[g][EB[i]]);
     }
-  // permutations sigma of the face's three vertices (lexicographic order):
-  // the point with barycentrics lambda becomes the point with lambda o sigma
+  // The neighbour's face f2 with its vertices in the order of permutation s
+  // (lexicographic): its face vertex j is the own face vertex s[j].
+  static const int FV[4][3] = {{1, 2, 3}, {0, 2, 3}, {0, 1, 3}, {0, 1, 2}};
   static const int SIG[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-  for (int sg = 0; sg < 6; ++sg)
-    for (int g = 0; g < TET_NFP; ++g) {
-      int found = -1;
-      for (int h = 0; h < TET_NFP && found < 0; ++h) {
-        bool same = true;
-        for (int j = 0; j < 3; ++j) same = same && std::fabs(bary[h][j] - bary[g][SIG[sg][j]]) < 1e-12;
-        if (same) found = h;
+  auto node_at = [&](const double* x) {
+    for (int j = 0; j < n; ++j)
+      if (std::fabs(nodes[j][0] - x[0]) + std::fabs(nodes[j][1] - x[1]) + std::fabs(nodes[j][2] - x[2]) < 1e-9) return j;
+    return -1;
+  };
+  for (int f2 = 0; f2 < 4; ++f2)
+    for (int sg = 0; sg < 6; ++sg) {
+      int own[3];                  // the neighbour's vertex at own face vertex i
+      for (int j = 0; j < 3; ++j) own[SIG[sg][j]] = FV[f2][j];
+      uint32_t pk = 0;
+      for (int i = 0; i < (p == 1 ? 3 : 6); ++i) {
+        const double* xa = RV[own[i < 3 ? i : EA[i - 3]]];
+        const double* xb = RV[own[i < 3 ? i : EB[i - 3]]];
+        const double x[3] = {0.5 * (xa[0] + xb[0]), 0.5 * (xa[1] + xb[1]), 0.5 * (xa[2] + xb[2])};
+        pk |= static_cast<uint32_t>(node_at(x)) << (4 * i);
       }
-      T.perm[sg][g] = static_cast<int8_t>(found);
+      T.fmap[8 * f2 + sg] = pk;
     }
 }
 

@@ -18,9 +18,9 @@
 //    weights from the density).
 //
 // A face's points are Radon's symmetric rule; the neighbour's trace at the
-// cell's own point g is the neighbour's basis at its rule point perm[s][g],
-// s the permutation between the two cells' orders of the face's vertices
-// (packed with the neighbour's id and face by the mesh build).
+// cell's own points comes from its nodes in the order of the own face's
+// (fmap, by the neighbour's face and the permutation between the two cells'
+// orders of the face's vertices, packed with its id by the mesh build).
 #include "cvw_device.h"
 #include "cvw_cells3d.h"
 
@@ -410,13 +410,45 @@ __device__ __forceinline__ void tet_hll(const MethodScalars& ms, const float* um
   }
 }
 
+// the nodes of face f: its vertices a < b < c, for P = 2 then the midpoints ab, ac, bc
+template <int P>
+struct TetFace {
+  static constexpr int NF = (P + 1) * (P + 2) / 2;
+  int n[4][NF];
+  constexpr TetFace() : n{} {
+    const int V[4][3] = {{1, 2, 3}, {0, 2, 3}, {0, 1, 3}, {0, 1, 2}};
+    const int vert[4] = {0, P == 1 ? 1 : 2, P == 1 ? 2 : 5, P == 1 ? 3 : 9};
+    const int mid[4][4] = {{0, 1, 3, 6}, {1, 0, 4, 7}, {3, 4, 0, 8}, {6, 7, 8, 0}};
+    for (int f = 0; f < 4; ++f)
+      for (int i = 0; i < 3; ++i) {
+        n[f][i] = vert[V[f][i]];
+        if (P == 2) n[f][NF - 3 + i] = mid[V[f][i == 2 ? 1 : 0]][V[f][i == 0 ? 1 : 2]];
+      }
+  }
+};
+template <int P>
+inline constexpr TetFace<P> tet_face{};
+
+// Cell pass, one thread per cell.  A polynomial of the cell is kept as its
+// monomial coefficients about the centroid (c[0]; x, y, z; for P = 2 xx, xy,
+// xz, yy, yz, zz, the squares' doubled; from differences, so that constants
+// have zero gradients; about a vertex the residual's error is 1.4 times as
+// large).  The volume points lie on lines along x, on which a variable is one
+// polynomial in x: values and gradients cost a few multiply-adds per point,
+// and the test functions' gradients, affine too, need only the moments of the
+// flux in 1, x, y, z.  A face's trace depends on its nodes alone; the
+// neighbour's are read in the order of the own face.  VALU bound: 13,000
+// instructions per wavefront of P_2 Euler cells, two wavefronts per SIMD at
+// 226 registers (three would spill: 209 us).  300,366 cells, residual: 171 us
+// against 273 with the basis and its gradients applied node by node at every
+// point (24,900 instructions).
 template <int P, int FLUX>
 __global__ __launch_bounds__(TET_THREADS) void tet_eval_kernel(
     const float* __restrict__ u, const float* __restrict__ u0, float* __restrict__ out, float* __restrict__ gamma_out,
     float* __restrict__ alpha_out, const float* __restrict__ gamma_in, const int32_t* __restrict__ nbrt, const double* __restrict__ geot, const TetTables* __restrict__ tab, int64_t E,
     MethodScalars ms, int mode, float dt, float a0, float b0, uint32_t* __restrict__ status) {
   using S = TetShape<P>;
-  constexpr int NLOC = S::NLOC, NK = S::NK, NQ = S::NQ, NV = TetNV<FLUX>::value;
+  constexpr int NLOC = S::NLOC, NQ = S::NQ, NV = TetNV<FLUX>::value, N1 = P + 1, NF = TetFace<P>::NF;
   const int tid = threadIdx.x;
   const int64_t e = static_cast<int64_t>(blockIdx.x) * TET_THREADS + tid;
   if (e >= E) return;
@@ -427,7 +459,7 @@ __global__ __launch_bounds__(TET_THREADS) void tet_eval_kernel(
   for (int v = 0; v < NV; ++v)
 #pragma unroll
     for (int j = 0; j < NLOC; ++j) uv[v][j] = u[(v * E + e) * NLOC + j];
-  const double h2 = G.h * G.h;
+  const int4 nb4 = reinterpret_cast<const int4*>(nbrt)[e];
 
   // ---- gamma_e: from the sensor pass, or the fixed value
   const float gam = ms.sensor_kind != CVW_SENSOR_FIXED ? gamma_in[e] : ms.fixed_gamma;
@@ -438,18 +470,83 @@ __global__ __launch_bounds__(TET_THREADS) void tet_eval_kernel(
   for (int b = 0; b < 3; ++b)
 #pragma unroll
     for (int a = 0; a < 3; ++a) A[b][a] = static_cast<float>(G.A[b][a]);
+  float n0[3];                                 // -grad lambda_0
+#pragma unroll
+  for (int a = 0; a < 3; ++a) n0[a] = static_cast<float>(G.A[0][a] + G.A[1][a] + G.A[2][a]);
   const float fdet = static_cast<float>(G.det);
+  // monomial coefficients about the centroid
+  float c[NV][NLOC];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const float* w = uv[v];
+    if constexpr (P == 1) {
+#pragma unroll
+      for (int j = 1; j < 4; ++j) c[v][j] = w[j] - w[0];
+      c[v][0] = fmaf(0.25f, c[v][1] + c[v][2] + c[v][3], w[0]);
+    } else {
+      // at the centroid the vertex functions have value -1/8 and gradient 0,
+      // the midpoint functions 1/4 and the sum of their two grad lambda
+      const float x1 = 4.0f * (w[1] - w[0]), x2 = w[2] - w[0], y1 = 4.0f * (w[3] - w[0]), y2 = w[5] - w[0];
+      const float z1 = 4.0f * (w[6] - w[0]), z2 = w[9] - w[0];
+      const float xy = 4.0f * (w[4] - w[0]), xz = 4.0f * (w[7] - w[0]), yz = 4.0f * (w[8] - w[0]);
+      c[v][0] = w[0] + (0.0625f * ((x1 + y1 + z1) + (xy + xz + yz)) - 0.125f * (x2 + y2 + z2));
+      c[v][1] = (w[4] - w[3]) + (w[7] - w[6]);
+      c[v][2] = (w[4] - w[1]) + (w[8] - w[6]);
+      c[v][3] = (w[7] - w[1]) + (w[8] - w[3]);
+      c[v][4] = 2.0f * (2.0f * x2 - x1);
+      c[v][5] = xy - x1 - y1;
+      c[v][6] = xz - x1 - z1;
+      c[v][7] = 2.0f * (2.0f * y2 - y1);
+      c[v][8] = yz - y1 - z1;
+      c[v][9] = 2.0f * (2.0f * z2 - z1);
+    }
+  }
+  // a variable on the line t: l[0] + l[1] x (+ l[2] x^2 / 2), and the physical
+  // gradient there: p + q x
+  auto line_val = [&](int v, const float* t, float (&l)[3]) {
+    const float y = t[0], z = t[1], yh = t[2], zh = t[3];
+    if constexpr (P == 1) {
+      l[0] = fmaf(c[v][2], y, fmaf(c[v][3], z, c[v][0]));
+      l[1] = c[v][1];
+      l[2] = 0.0f;
+    } else {
+      const float ty = fmaf(c[v][8], z, fmaf(c[v][7], yh, c[v][2]));
+      const float tz = fmaf(c[v][9], zh, c[v][3]);
+      l[0] = fmaf(ty, y, fmaf(tz, z, c[v][0]));
+      l[1] = fmaf(c[v][5], y, fmaf(c[v][6], z, c[v][1]));
+      l[2] = c[v][4];
+    }
+  };
+  auto line_grad = [&](int v, const float* t, float (&p)[3], float (&q)[3]) {
+    const float y = t[0], z = t[1];
+    float gx = c[v][1], gy = c[v][2], gz = c[v][3];
+    if constexpr (P == 2) {
+      gx = fmaf(c[v][5], y, fmaf(c[v][6], z, gx));
+      gy = fmaf(c[v][8], z, fmaf(c[v][7], y, gy));
+      gz = fmaf(c[v][8], y, fmaf(c[v][9], z, gz));
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      p[a] = fmaf(A[0][a], gx, fmaf(A[1][a], gy, A[2][a] * gz));
+      q[a] = P == 1 ? 0.0f : fmaf(A[1][a], c[v][P == 1 ? 0 : 5], fmaf(A[2][a], c[v][P == 1 ? 0 : 6], A[0][a] * c[v][P == 1 ? 0 : 4]));
+    }
+  };
+  auto line_at = [&](const float (&l)[3], const float* t, int i) {
+    return P == 1 ? fmaf(l[1], t[4 + i], l[0]) : fmaf(fmaf(l[2], t[7 + i], l[1]), t[4 + i], l[0]);
+  };
+
   // second derivatives of the sensor field (P = 2; constant), for alpha~
   float hs2 = 0.0f;
   if constexpr (P >= 2) {
-    double R[NK];
+    double R[S::NK] = {}, D[S::NK], w[NLOC];
 #pragma unroll
-    for (int k = 0; k < NK; ++k) R[k] = 0.0;
-#pragma unroll
-    for (int t = 0; t < 6; ++t)
-#pragma unroll
-      for (int j = 0; j < NLOC; ++j) R[3 + t] = fma(tab->H2[t][j], static_cast<double>(uv[0][j]), R[3 + t]);
-    double D[NK];
+    for (int j = 0; j < NLOC; ++j) w[j] = static_cast<double>(uv[0][j]);
+    R[3] = 4.0 * ((w[2] - w[1]) - (w[1] - w[0]));
+    R[4] = 4.0 * ((w[4] - w[3]) - (w[1] - w[0]));
+    R[5] = 4.0 * ((w[7] - w[6]) - (w[1] - w[0]));
+    R[6] = 4.0 * ((w[5] - w[3]) - (w[3] - w[0]));
+    R[7] = 4.0 * ((w[8] - w[6]) - (w[3] - w[0]));
+    R[8] = 4.0 * ((w[9] - w[6]) - (w[6] - w[0]));
     tet_phys<P>(G.A, R, D);
 #pragma unroll
     for (int t = 0; t < 6; ++t) hs2 += static_cast<float>(D[3 + t] * D[3 + t]);
@@ -458,162 +555,222 @@ __global__ __launch_bounds__(TET_THREADS) void tet_eval_kernel(
   if (!(lam > 0.0f)) {
     const float vn = fsqrt(ms.fp[0] * ms.fp[0] + ms.fp[1] * ms.fp[1] + ms.fp[2] * ms.fp[2]);
     lam = 0.0f;
-    for (int q = 0; q < NQ; ++q) {
-      float uq[NV];
+#pragma unroll 1
+    for (int k = 0; k < N1 * N1; ++k) {
+      const float* t = tab->line[k];
+      float l[NV][3];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        uq[v] = 0.0f;
+      for (int v = 0; v < NV; ++v) line_val(v, t, l[v]);
 #pragma unroll
-        for (int j = 0; j < NLOC; ++j) uq[v] = fmaf(tab->Bs[q][j], uv[v][j], uq[v]);
+      for (int i = 0; i < N1; ++i) {
+        float uq[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) uq[v] = line_at(l[v], t, i);
+        float sp;
+        if constexpr (FLUX == CVW_EULER) {
+          float vel[3];
+          const float pq = tet_prim(ms, uq, vel);
+          sp = fsqrt(vel[0] * vel[0] + vel[1] * vel[1] + vel[2] * vel[2]) + fsqrt(fmaxf(ms.fp[0] * pq * frcp(uq[0]), 0.0f));
+        } else {
+          sp = FLUX == CVW_BURGERS ? fabsf(uq[0]) * vn : vn;
+        }
+        lam = fmaxf(lam, sp);
       }
-      float sp;
-      if constexpr (FLUX == CVW_EULER) {
-        float vel[3];
-        const float pq = tet_prim(ms, uq, vel);
-        sp = fsqrt(vel[0] * vel[0] + vel[1] * vel[1] + vel[2] * vel[2]) + fsqrt(fmaxf(ms.fp[0] * pq * frcp(uq[0]), 0.0f));
-      } else {
-        sp = FLUX == CVW_BURGERS ? fabsf(uq[0]) * vn : vn;
-      }
-      lam = fmaxf(lam, sp);
     }
   }
   const float nu = lam * static_cast<float>(G.h) / (2.0f * P);
   // SC weights (sensor field): S = sum W f, T = sum W alpha~ f over the volume points
   const bool sc_active = ms.sc_on && gam < ms.c_gamma;
   float Sv = 0.0f, Tv = 0.0f;
-  const float fh2 = static_cast<float>(h2);
+  const float fh2 = static_cast<float>(G.h * G.h);
+  const float ah2 = fh2 * fh2 * hs2;
   if (sc_active) {
-    for (int q = 0; q < NQ; ++q) {
-      float gr[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int k = 0; k < N1 * N1; ++k) {
+      const float* t = tab->line[k];
+      float p[3], q[3];
+      line_grad(0, t, p, q);
 #pragma unroll
-      for (int j = 0; j < NLOC; ++j)
+      for (int i = 0; i < N1; ++i) {
+        float g2 = 0.0f;
 #pragma unroll
-        for (int b = 0; b < 3; ++b) gr[b] = fmaf(tab->Gs[b][q][j], uv[0][j], gr[b]);
-      float g2 = 0.0f;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const float d = A[0][a] * gr[0] + A[1][a] * gr[1] + A[2][a] * gr[2];
-        g2 = fmaf(d, d, g2);
+        for (int a = 0; a < 3; ++a) {
+          const float d = fmaf(q[a], t[4 + i], p[a]);
+          g2 = fmaf(d, d, g2);
+        }
+        const float W = t[10 + i] * fdet;
+        const float f = (1.0f - gam) * g2;
+        Sv = fmaf(W, f, Sv);
+        Tv = fmaf(W * fsqrt(fmaf(fh2, g2, ah2)), f, Tv);
       }
-      const float at = fsqrt(fh2 * g2 + fh2 * fh2 * hs2);
-      const float W = tab->wqs[q] * fdet;
-      const float f = (1.0f - gam) * g2;
-      Sv = fmaf(W, f, Sv);
-      Tv = fmaf(W * at, f, Tv);
     }
   }
   const bool use_alpha = sc_active && Sv > 0.0f && Tv > 0.0f;
   const float ratioST = use_alpha ? Sv / Tv : 0.0f;
-  float r[NV][NLOC];
+  const float nug = nu * (1.0f - gam);
+
+  // ---- volume terms: the moments of V = w (nu alpha (1 - gamma) grad u - f(u))
+  // in reference components, M[v]: V_x, V_y, V_z; for P = 2 also x V_x,
+  // y V_x + x V_y, z V_x + x V_z, y V_y, z V_y + y V_z, z V_z
+  float M[NV][NLOC - 1];
 #pragma unroll
   for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int j = 0; j < NLOC; ++j) r[v][j] = 0.0f;
-  for (int q = 0; q < NQ; ++q) {
-    float uq[NV], gp[NV][3];
+    for (int k = 0; k < NLOC - 1; ++k) M[v][k] = 0.0f;
+#pragma unroll 1
+  for (int k = 0; k < N1 * N1; ++k) {
+    const float* t = tab->line[k];
+    const float y = t[0], z = t[1];
+    float uq[NV][N1], gs[N1];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      float gr[3] = {0.0f, 0.0f, 0.0f};
-      uq[v] = 0.0f;
+      float l[3];
+      line_val(v, t, l);
 #pragma unroll
-      for (int j = 0; j < NLOC; ++j) {
-        uq[v] = fmaf(tab->Bs[q][j], uv[v][j], uq[v]);
-#pragma unroll
-        for (int b = 0; b < 3; ++b) gr[b] = fmaf(tab->Gs[b][q][j], uv[v][j], gr[b]);
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) gp[v][a] = A[0][a] * gr[0] + A[1][a] * gr[1] + A[2][a] * gr[2];
+      for (int i = 0; i < N1; ++i) uq[v][i] = line_at(l, t, i);
     }
-    float alpha = 1.0f;
+#pragma unroll
+    for (int i = 0; i < N1; ++i) gs[i] = 1.0f;
     if (use_alpha) {
-      const float g2 = gp[0][0] * gp[0][0] + gp[0][1] * gp[0][1] + gp[0][2] * gp[0][2];
-      alpha = fsqrt(fh2 * g2 + fh2 * fh2 * hs2) * ratioST;
+      float p[3], q[3];
+      line_grad(0, t, p, q);
+#pragma unroll
+      for (int i = 0; i < N1; ++i) {
+        float g2 = 0.0f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const float d = fmaf(q[a], t[4 + i], p[a]);
+          g2 = fmaf(d, d, g2);
+        }
+        gs[i] = fsqrt(fmaf(fh2, g2, ah2)) * ratioST;
+      }
     }
-    const float W = tab->wqs[q] * fdet;
-    const float gs = nu * alpha * (1.0f - gam);
     if (mode == MODE_SENSOR) {
-      if (alpha_out) alpha_out[e * NQ + q] = alpha;
+      if (alpha_out)
+#pragma unroll
+        for (int i = 0; i < N1; ++i) alpha_out[e * NQ + N1 * k + i] = gs[i];
       continue;
     }
-    float vel[3] = {0.0f, 0.0f, 0.0f}, pres = 0.0f;
-    if constexpr (FLUX == CVW_EULER) pres = tet_prim(ms, uq, vel);
+    float inv[N1], pres[N1];                 // 1 / rho and pressure (Euler)
+#pragma unroll
+    for (int i = 0; i < N1; ++i) {
+      gs[i] *= nug;
+      pres[i] = inv[i] = 0.0f;
+      if constexpr (FLUX == CVW_EULER) {
+        inv[i] = frcp(uq[0][i]);
+        const float m2 = uq[1][i] * uq[1][i] + uq[2][i] * uq[2][i] + uq[3][i] * uq[3][i];
+        pres[i] = (ms.fp[0] - 1.0f) * (uq[4][i] - 0.5f * m2 * inv[i]);
+      }
+    }
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      float V[3];
+      float p[3], q[3], S0[3] = {0.0f, 0.0f, 0.0f}, S1[3] = {0.0f, 0.0f, 0.0f};
+      line_grad(v, t, p, q);
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        float fa;
-        if constexpr (FLUX == CVW_EULER)   // f_a of variable v: m_a, m_c v_a + p delta_ca, (E + p) v_a
-          fa = v == 0 ? uq[1 + a] : (v < 4 ? uq[v] * vel[a] + (v - 1 == a ? pres : 0.0f) : (uq[4] + pres) * vel[a]);
-        else
-          fa = FLUX == CVW_BURGERS ? 0.5f * uq[0] * uq[0] * ms.fp[a] : ms.fp[a] * uq[0];
-        V[a] = W * (gs * gp[v][a] - fa);
+      for (int i = 0; i < N1; ++i) {
+        const float w = t[10 + i], wx = t[13 + i];
+        // Euler: f_a of variable v: m_a, m_c v_a + p delta_ca, (E + p) v_a = h m_a (+ p delta_ca)
+        float h = 0.0f;
+        if constexpr (FLUX == CVW_EULER) h = (v < 4 ? uq[v][i] : uq[4][i] + pres[i]) * inv[i];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          float fa;
+          if constexpr (FLUX == CVW_EULER)
+            fa = v == 0 ? uq[1 + a][i] : h * uq[1 + a][i] + (v - 1 == a ? pres[i] : 0.0f);
+          else
+            fa = FLUX == CVW_BURGERS ? 0.5f * uq[0][i] * uq[0][i] * ms.fp[a] : ms.fp[a] * uq[0][i];
+          const float V = gs[i] * (P == 1 ? p[a] : fmaf(q[a], t[4 + i], p[a])) - fa;
+          S0[a] = fmaf(w, V, S0[a]);
+          if constexpr (P == 2) S1[a] = fmaf(wx, V, S1[a]);
+        }
       }
-      float Vr[3];
+      float r0[3], r1[3];
 #pragma unroll
-      for (int b = 0; b < 3; ++b) Vr[b] = A[b][0] * V[0] + A[b][1] * V[1] + A[b][2] * V[2];
-#pragma unroll
-      for (int j = 0; j < NLOC; ++j)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) r[v][j] = fmaf(tab->Gs[b][q][j], Vr[b], r[v][j]);
+      for (int b = 0; b < 3; ++b) {
+        r0[b] = A[b][0] * S0[0] + A[b][1] * S0[1] + A[b][2] * S0[2];
+        r1[b] = P == 1 ? 0.0f : A[b][0] * S1[0] + A[b][1] * S1[1] + A[b][2] * S1[2];
+        M[v][b] += r0[b];
+      }
+      if constexpr (P == 2) {
+        M[v][3] += r1[0];
+        M[v][4] += fmaf(y, r0[0], r1[1]);
+        M[v][5] += fmaf(z, r0[0], r1[2]);
+        M[v][6] = fmaf(y, r0[1], M[v][6]);
+        M[v][7] = fmaf(z, r0[1], fmaf(y, r0[2], M[v][7]));
+        M[v][8] = fmaf(z, r0[2], M[v][8]);
+      }
     }
   }
   if (mode == MODE_SENSOR) {
     if (gamma_out) gamma_out[e] = gam;
     return;
   }
-
-  // ---- interface terms (face f opposite vertex f)
-  float xvf[4][3];
+  // sum_q V . grad phi_j from the moments: the transpose of the coefficients
+  float r[NV][NLOC];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    xvf[0][a] = 0.0f;
+  for (int v = 0; v < NV; ++v) {
+    float m[NLOC - 1];
 #pragma unroll
-    for (int l = 1; l < 4; ++l) xvf[l][a] = static_cast<float>(G.J[a][l - 1]);   // relative to vertex 0
-  }
-#pragma unroll(NV == 1 ? 4 : 1)
-  for (int f = 0; f < 4; ++f) {
-    const int32_t code = nbrt[e * 4 + f];
-    const int64_t e2 = code >> 5;
-    const int f2 = (code >> 3) & 3, sg = code & 7;
-    float va[3], vb[3], vc[3], vo[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {     // the face's vertices and the opposite one (a select: f may be a loop variable)
-      float x0 = xvf[0][a], x1 = xvf[1][a], x2 = xvf[2][a], x3 = xvf[3][a];
-      va[a] = f == 0 ? x1 : x0;
-      vb[a] = f <= 1 ? x2 : x1;
-      vc[a] = f <= 2 ? x3 : x2;
-      vo[a] = f == 0 ? x0 : (f == 1 ? x1 : (f == 2 ? x2 : x3));
+    for (int k = 0; k < NLOC - 1; ++k) m[k] = M[v][k] * fdet;
+    if constexpr (P == 1) {
+      r[v][0] = -(m[0] + m[1] + m[2]);
+      r[v][1] = m[0];
+      r[v][2] = m[1];
+      r[v][3] = m[2];
+    } else {
+      r[v][0] = 4.0f * ((m[3] + m[6] + m[8]) + (m[4] + m[5] + m[7]));
+      r[v][1] = -(m[1] + m[2]) - 4.0f * (2.0f * m[3] + m[4] + m[5]);
+      r[v][2] = 4.0f * m[3];
+      r[v][3] = -(m[0] + m[2]) - 4.0f * (2.0f * m[6] + m[4] + m[7]);
+      r[v][4] = (m[0] + m[1]) + 4.0f * m[4];
+      r[v][5] = 4.0f * m[6];
+      r[v][6] = -(m[0] + m[1]) - 4.0f * (2.0f * m[8] + m[5] + m[7]);
+      r[v][7] = (m[0] + m[2]) + 4.0f * m[5];
+      r[v][8] = (m[1] + m[2]) + 4.0f * m[7];
+      r[v][9] = 4.0f * m[8];
     }
-    const float t1[3] = {vb[0] - va[0], vb[1] - va[1], vb[2] - va[2]};
-    const float t2[3] = {vc[0] - va[0], vc[1] - va[1], vc[2] - va[2]};
-    float n[3] = {t1[1] * t2[2] - t1[2] * t2[1], t1[2] * t2[0] - t1[0] * t2[2], t1[0] * t2[1] - t1[1] * t2[0]};
-    const float jf = fsqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-    const float ij = 1.0f / jf;
-    const float side = n[0] * (vo[0] - va[0]) + n[1] * (vo[1] - va[1]) + n[2] * (vo[2] - va[2]);
-    const float sgn = side > 0.0f ? -ij : ij;          // outward: away from the opposite vertex
+  }
+
+  // ---- interface terms (face f opposite vertex f): the outward normal is
+  // -grad lambda_f / |grad lambda_f|, the face Jacobian |det J| |grad lambda_f|
+  // The cell's values are read again: their registers are needed meanwhile.
+  int64_t er = e;
+  asm volatile("" : "+v"(er));
 #pragma unroll
-    for (int a = 0; a < 3; ++a) n[a] *= sgn;
-    float un[NV][NLOC];
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int j = 0; j < NLOC; ++j) uv[v][j] = u[(v * E + er) * NLOC + j];
+  // one face per copy of the code (its nodes are registers), its points rolled
+  const int32_t codes[4] = {nb4.x, nb4.y, nb4.z, nb4.w};
+#pragma unroll
+  for (int f = 0; f < 4; ++f) {
+    const int64_t e2 = codes[f] >> 5;
+    const uint32_t pk = tab->fmap[codes[f] & 31];
+    float un[NV][NF];
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-      for (int j = 0; j < NLOC; ++j) un[v][j] = u[(v * E + e2) * NLOC + j];
-    float lfv = 0.0f;
-    if constexpr (FLUX != CVW_BURGERS) lfv = fabsf(ms.fp[0] * n[0] + ms.fp[1] * n[1] + ms.fp[2] * n[2]);
-    const float bn = fabsf(ms.fp[0] * n[0] + ms.fp[1] * n[1] + ms.fp[2] * n[2]);
+      for (int i = 0; i < NF; ++i) un[v][i] = u[(v * E + e2) * NLOC + ((pk >> (4 * i)) & 15)];
+    float n[3];
 #pragma unroll
+    for (int a = 0; a < 3; ++a) n[a] = f == 0 ? n0[a] : -A[f == 0 ? 0 : f - 1][a];
+    const float na = fsqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]), ina = 1.0f / na;
+    const float jf = fabsf(fdet) * na;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) n[a] *= ina;
+    const float bn = fabsf(ms.fp[0] * n[0] + ms.fp[1] * n[1] + ms.fp[2] * n[2]);
+#pragma unroll 1
     for (int g = 0; g < TET_NFP; ++g) {
-      const int g2 = tab->perm[sg][g];
+      const float* B = tab->Bt[g];
       float um[NV], up[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        um[v] = 0.0f;
-        up[v] = 0.0f;
+        um[v] = B[0] * uv[v][tet_face<P>.n[f][0]];
+        up[v] = B[0] * un[v][0];
 #pragma unroll
-        for (int j = 0; j < NLOC; ++j) {
-          um[v] = fmaf(tab->Bf[f][g][j], uv[v][j], um[v]);
-          up[v] = fmaf(tab->Bf[f2][g2][j], un[v][j], up[v]);
+        for (int i = 1; i < NF; ++i) {
+          um[v] = fmaf(B[i], uv[v][tet_face<P>.n[f][i]], um[v]);
+          up[v] = fmaf(B[i], un[v][i], up[v]);
         }
       }
       float fs[NV];
@@ -621,44 +778,52 @@ __global__ __launch_bounds__(TET_THREADS) void tet_eval_kernel(
         tet_hll(ms, um, up, n, fs);
       } else {
         float lf = ms.lam_g;
-        if (!(lf > 0.0f)) lf = FLUX == CVW_BURGERS ? fmaxf(fabsf(um[0]), fabsf(up[0])) * bn : lfv;
+        if (!(lf > 0.0f)) lf = FLUX == CVW_BURGERS ? fmaxf(fabsf(um[0]), fabsf(up[0])) * bn : bn;
         fs[0] = 0.5f * (tet_fn<FLUX>(ms, um[0], n) + tet_fn<FLUX>(ms, up[0], n)) - 0.5f * lf * (up[0] - um[0]);
       }
+      const float wj = tab->wf[g] * jf;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const float w = tab->wf[g] * jf * fs[v];
+        const float w = wj * fs[v];
 #pragma unroll
-        for (int j = 0; j < NLOC; ++j) r[v][j] = fmaf(tab->Bf[f][g][j], w, r[v][j]);
+        for (int i = 0; i < NF; ++i) {
+          float& x = r[v][tet_face<P>.n[f][i]];
+          x = fmaf(B[i], w, x);
+        }
       }
     }
   }
 
-  // ---- output
+  // ---- output: r, or u_out = a0 u_n + b0 (u - dt M_e^{-1} r), M_e = det J M_ref
   bool nonfinite = false;
-  if (mode == MODE_RESIDUAL) {
+  const float scl = dt / fdet;
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
+  for (int v = 0; v < NV; ++v) {
+    const int64_t idx = (v * E + e) * NLOC;
+    float o[NLOC];
+    if (mode == MODE_RESIDUAL) {
 #pragma unroll
-      for (int j = 0; j < NLOC; ++j) {
-        nonfinite = nonfinite || !isfinite(r[v][j]);
-        out[(v * E + e) * NLOC + j] = r[v][j];
-      }
-  } else {
-    // u_out = a0 u_n + b0 (u - dt M_e^{-1} r), M_e = det J M_ref
-    const float scl = dt / fdet;
+      for (int j = 0; j < NLOC; ++j) o[j] = r[v][j];
+    } else {
+      float base[NLOC];
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
+      for (int j = 0; j < NLOC; ++j) base[j] = 0.0f;
+      if (a0 != 0.0f)
+#pragma unroll
+        for (int j = 0; j < NLOC; ++j) base[j] = a0 * u0[idx + j];
 #pragma unroll
       for (int j = 0; j < NLOC; ++j) {
         float x = 0.0f;
 #pragma unroll
         for (int i = 0; i < NLOC; ++i) x = fmaf(tab->Minv[j][i], r[v][i], x);
-        const int64_t idx = (v * E + e) * NLOC + j;
-        const float base = (a0 != 0.0f) ? a0 * u0[idx] : 0.0f;
-        const float o = base + b0 * (uv[v][j] - scl * x);
-        nonfinite = nonfinite || !isfinite(o);
-        out[idx] = o;
+        o[j] = base[j] + b0 * (uv[v][j] - scl * x);
       }
+    }
+#pragma unroll
+    for (int j = 0; j < NLOC; ++j) {
+      nonfinite |= !isfinite(o[j]);
+      out[idx + j] = o[j];
+    }
   }
   if (gamma_out) gamma_out[e] = gam;
   if (nonfinite) atomicOr(status, ST_NONFINITE);
