@@ -488,4 +488,13 @@ __device__ __forceinline__ BatchRun batch_run(const BatchList& l, int first) {
   return {static_cast<int>(lo < l.n ? lo : l.n), static_cast<int>(lo + l.run < l.n ? lo + l.run : l.n)};
 }
 
+// For exchanges inside one wavefront through LDS slots of its own: they need
+// only the wavefront's LDS operations kept in program order (they complete in
+// issue order), not a workgroup barrier.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace cvw

@@ -63,15 +63,6 @@ __device__ __forceinline__ float team_maxf(float x) {
   return x;
 }
 
-// A team lives inside one wavefront and its LDS slots are its own: an
-// exchange needs only the wavefront's LDS operations kept in program order
-// (they complete in issue order), not a workgroup barrier.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // scalar fluxes in 3D: f_d(u) = v_d u (constant advection) or u^2 / 2 b_d (Burgers)
 template <int FLUX>
 __device__ __forceinline__ float hex_flux(const MethodScalars& ms, float u, int d) {

@@ -152,7 +152,7 @@ __device__ __forceinline__ void cell_moments(const TriGeo& G, const TriTables* _
 #pragma unroll
   for (int i = 0; i < NMOM<P>; ++i) mu[i] = 0.0;
   const double adet = fabs(G.det);
-#pragma unroll 1
+#pragma unroll 4
   for (int q = 0; q < NQ; ++q) {
     const double xi = tab->xqd[q], eta = tab->yqd[q];
     mom_add<P>(tab->wqd[q] * adet, G.J[0][0] * xi + G.J[0][1] * eta, G.J[1][0] * xi + G.J[1][1] * eta, mu);
@@ -335,6 +335,11 @@ __global__ __launch_bounds__(256) void tri_limit_kernel(const float* __restrict_
 }
 
 // ---------------------------------------------------------------------------
+// Bound by the vector memory pipe and latency: the derivative tables, indexed
+// by the lane's local vertex, took 55 wide loads per cell (880 cycles of it)
+// from the cache; from LDS, and with the next cell's values requested ahead,
+// P_3 on 262,144 vertices takes 29 us against 46.  (Eight lanes per vertex,
+// their terms added in patch order through LDS: 56.)
 template <int P>
 __global__ __launch_bounds__(256) void tri_vertex_kernel(const float* __restrict__ u, float* __restrict__ cand,
                                                          const int32_t* __restrict__ vptr,
@@ -343,6 +348,10 @@ __global__ __launch_bounds__(256) void tri_vertex_kernel(const float* __restrict
                                                          const TriTables* __restrict__ tab, int64_t Nv,
                                                          MethodScalars ms) {
   constexpr int NLOC = (P + 1) * (P + 2) / 2, NK = NLOC - 1;
+  __shared__ double sTV[3][NK][NLOC];
+  for (int t = threadIdx.x; t < 3 * NK * NLOC; t += 256)
+    sTV[t / (NK * NLOC)][t / NLOC % NK][t % NLOC] = tab->TV[t / (NK * NLOC)][t / NLOC % NK][t % NLOC];
+  __syncthreads();
   // XCD-aware order: each XCD walks a contiguous range of vertices, so the
   // cells shared by neighbouring vertex rows are read again from its own L2
   const int64_t i = xcd_block(blockIdx.x, gridDim.x) * static_cast<int64_t>(blockDim.x) + threadIdx.x;
@@ -350,25 +359,44 @@ __global__ __launch_bounds__(256) void tri_vertex_kernel(const float* __restrict
   double num[NK], den = 0.0;
 #pragma unroll
   for (int k = 0; k < NK; ++k) num[k] = 0.0;
-  for (int it = vptr[i]; it < vptr[i + 1]; ++it) {
-    const int ent = vent[it];
+  const int beg = vptr[i], end = vptr[i + 1];
+  // the next cell's values and the id after it are requested before a cell is
+  // used (clamped, so that no wait sits at the loads)
+  float un[NLOC];
+  float4 gan, gbn;
+  int entn = 0, ent2 = 0;
+  if (beg < end) {
+    entn = vent[beg];
+    ent2 = vent[min(beg + 1, end - 1)];
+  }
+  auto fetch = [&](int ent) {
     const int64_t e = ent >> 2;
-    const int lv = ent & 3;
-    const float4 ga = geov[2 * e], gb = geov[2 * e + 1];   // A (row major), h_e
+#pragma unroll
+    for (int j = 0; j < NLOC; ++j) un[j] = u[e * NLOC + j];
+    gan = geov[2 * e];
+    gbn = geov[2 * e + 1];
+  };
+  fetch(entn);
+#pragma unroll 1
+  for (int it = beg; it < end; ++it) {
+    const int lv = entn & 3;
+    const float4 ga = gan, gb = gbn;   // A (row major), h_e
+    double uc[NLOC];
+    const double u0 = static_cast<double>(un[0]);
+#pragma unroll
+    for (int j = 0; j < NLOC; ++j) uc[j] = static_cast<double>(un[j]) - u0;
+    entn = ent2;
+    fetch(entn);
+    ent2 = vent[min(it + 2, end - 1)];
     const double A[2][2] = {{static_cast<double>(ga.x), static_cast<double>(ga.y)},
                             {static_cast<double>(ga.z), static_cast<double>(ga.w)}};
     const double h = static_cast<double>(gb.x);
-    double uc[NLOC];
-    const float* ue = u + e * NLOC;
-    const double u0 = static_cast<double>(ue[0]);
-#pragma unroll
-    for (int j = 0; j < NLOC; ++j) uc[j] = static_cast<double>(ue[j]) - u0;
     double R[NK], H[NK];
 #pragma unroll
     for (int m = 0; m < NK; ++m) {
       double s = 0.0;
 #pragma unroll
-      for (int j = 1; j < NLOC; ++j) s = fma(tab->TV[lv][m][j], uc[j], s);
+      for (int j = 1; j < NLOC; ++j) s = fma(sTV[lv][m][j], uc[j], s);
       R[m] = s;
     }
     phys_from_ref<P>(A, R, H);
@@ -391,9 +419,14 @@ __global__ __launch_bounds__(256) void tri_vertex_kernel(const float* __restrict
 // ---------------------------------------------------------------------------
 constexpr int TRI_EVAL_THREADS = 128;
 
-// OPEN: the mesh has boundary faces (negative neighbour codes)
+// OPEN: the mesh has boundary faces (negative neighbour codes).  Bound by VALU
+// issue (half of it float64) and the waits for the scalar loads of the tables:
+// two volume points and four moment points at a time, and for the scalar laws
+// at P = 3 three wavefronts per SIMD (180 registers made two), 99 us against
+// 109 (KPP, 524,288 cells).  The Euler variants spill at that bound (96 us
+// against 80 on 84,000 cells) and keep their registers.
 template <int P, int FLUX, bool OPEN>
-__global__ __launch_bounds__(TRI_EVAL_THREADS) void tri_eval_kernel(const float* __restrict__ u, const float* __restrict__ u0,
+__global__ __launch_bounds__(TRI_EVAL_THREADS, P == 3 && FLUX != CVW_EULER ? 3 : 1) void tri_eval_kernel(const float* __restrict__ u, const float* __restrict__ u0,
                                                        float* __restrict__ out, float* __restrict__ gamma_out,
                                                        float* __restrict__ alpha_out, const float* __restrict__ cand,
                                                        const int32_t* __restrict__ cell_vtx,
@@ -554,7 +587,7 @@ __global__ __launch_bounds__(TRI_EVAL_THREADS) void tri_eval_kernel(const float*
 #pragma unroll
     for (int j = 0; j < NLOC; ++j) r[v][j] = 0.0f;
   const float cbase = nu * (1.0f - gf);
-#pragma unroll 1
+#pragma unroll 2
   for (int q = 0; q < NQ; ++q) {
     float uq[NV], ux[NV], uy[NV];
 #pragma unroll
@@ -650,7 +683,7 @@ __global__ __launch_bounds__(TRI_EVAL_THREADS) void tri_eval_kernel(const float*
     for (int v = 0; v < NV; ++v)
 #pragma unroll
       for (int j = 0; j < NLOC; ++j) {
-        nonfinite = nonfinite || !isfinite(r[v][j]);
+        nonfinite |= !isfinite(r[v][j]);
         out[v * stride + e * NLOC + j] = r[v][j];
       }
   } else {
@@ -666,7 +699,7 @@ __global__ __launch_bounds__(TRI_EVAL_THREADS) void tri_eval_kernel(const float*
         const int64_t idx = v * stride + e * NLOC + j;
         const float base = (a0 != 0.0f) ? a0 * u0[idx] : 0.0f;
         const float o = base + b0 * (uv[v][j] - sc * x);
-        nonfinite = nonfinite || !isfinite(o);
+        nonfinite |= !isfinite(o);
         out[idx] = o;
       }
   }
