@@ -601,7 +601,10 @@ __device__ __forceinline__ void dgq_eval_body(
     if (nd && (a == 0 || a == P)) {
       const bool west = (a == 0);
       const int32_t code = nbr[e * 4 + (west ? 3 : 1)];
-      float up[NV];
+      // (element selects: a selected array would live in scratch memory)
+      float um[NV], up[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) um[v] = west ? tW[v] : tE[v];
       if (!OPEN || code >= 0) {
         const int64_t en = code;
 #pragma unroll
@@ -613,10 +616,10 @@ __device__ __forceinline__ void dgq_eval_body(
           up[v] = s2;
         }
       } else {
-        ghost_state<FLUX>(ms, code, west ? tW : tE, west ? -1.0f : 1.0f, 0.0f, up);
+        ghost_state<FLUX>(ms, code, um, west ? -1.0f : 1.0f, 0.0f, up);
       }
       float fs[NV];
-      num_flux<FLUX>(ms, west ? tW : tE, up, west ? -1.0f : 1.0f, 0.0f, 0.0f, 0.0f, fs);
+      num_flux<FLUX>(ms, um, up, west ? -1.0f : 1.0f, 0.0f, 0.0f, 0.0f, fs);
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         if (west) fW[v] = wb * G.hhy * fs[v];
@@ -626,7 +629,9 @@ __device__ __forceinline__ void dgq_eval_body(
     if (nd && (b == 0 || b == P)) {
       const bool south = (b == 0);
       const int32_t code = nbr[e * 4 + (south ? 0 : 2)];
-      float up[NV];
+      float um[NV], up[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) um[v] = south ? tS[v] : tN[v];
       if (!OPEN || code >= 0) {
         const int64_t en = code;
 #pragma unroll
@@ -638,10 +643,10 @@ __device__ __forceinline__ void dgq_eval_body(
           up[v] = s2;
         }
       } else {
-        ghost_state<FLUX>(ms, code, south ? tS : tN, 0.0f, south ? -1.0f : 1.0f, up);
+        ghost_state<FLUX>(ms, code, um, 0.0f, south ? -1.0f : 1.0f, up);
       }
       float fs[NV];
-      num_flux<FLUX>(ms, south ? tS : tN, up, 0.0f, south ? -1.0f : 1.0f, 0.0f, 0.0f, fs);
+      num_flux<FLUX>(ms, um, up, 0.0f, south ? -1.0f : 1.0f, 0.0f, 0.0f, fs);
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         if (south) fS[v] = wa * G.hhx * fs[v];
