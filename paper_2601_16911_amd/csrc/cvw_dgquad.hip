@@ -260,22 +260,25 @@ template <int P>
 __global__ __launch_bounds__(256) void dgq_vertex_kernel(const float* __restrict__ u, float* __restrict__ cand,
                                                          const int32_t* __restrict__ vptr,
                                                          const int32_t* __restrict__ vent, int64_t Nv,
-                                                         int64_t nbp, VertexTables vt, MethodScalars ms) {
-  dgq_vertex_body<P>(u, cand, vptr, vent, Nv, xcd_block(blockIdx.x, nbp), vt, ms);
+                                                         int64_t nbp, VertexTables vt, MethodScalars ms,
+                                                         int64_t ustride) {
+  // blockIdx.y: the variable
+  dgq_vertex_body<P>(u + blockIdx.y * ustride, cand + blockIdx.y * Nv * KSet<P>::NK, vptr, vent, Nv,
+                     xcd_block(blockIdx.x, nbp), vt, ms);
 }
 
 // The listed vertices vlist[0 .. *count) only (the grid covers every vertex;
-// threads past the count leave).
+// threads past the count leave); blockIdx.y: the variable.
 template <int P>
 __global__ __launch_bounds__(256) void dgq_vertex_list_kernel(const float* __restrict__ u, float* __restrict__ cand,
                                                               const int32_t* __restrict__ vptr,
                                                               const int32_t* __restrict__ vent, int64_t Nv,
                                                               VertexTables vt, MethodScalars ms,
                                                               const uint32_t* __restrict__ count,
-                                                              const int32_t* __restrict__ vlist) {
+                                                              const int32_t* __restrict__ vlist, int64_t ustride) {
   const int64_t k = blockIdx.x * 256LL + threadIdx.x;
   if (k >= static_cast<int64_t>(*count) || k >= Nv) return;
-  dgq_vertex_at<P>(u, cand, vptr, vent, vlist[k], vt, ms);
+  dgq_vertex_at<P>(u + blockIdx.y * ustride, cand + blockIdx.y * Nv * KSet<P>::NK, vptr, vent, vlist[k], vt, ms);
 }
 
 // ---------------------------------------------------------------------------
@@ -954,24 +957,25 @@ static int64_t pad8(int64_t n) { return (n + 7) / 8 * 8; }
 
 template <int P>
 static void launch_vertex(const cvw_mesh* m, const MethodScalars& ms, const float* u, float* cand,
-                          const uint32_t* vcount, const int32_t* vlist, hipStream_t s) {
+                          const uint32_t* vcount, const int32_t* vlist, int nvar, hipStream_t s) {
   const int64_t nb = pad8((m->Nv + VTX_PER_BLOCK - 1) / VTX_PER_BLOCK);
   const VertexTables vt = make_vertex_tables(m->tens, m->hx, m->hy, m->he, P);
   if (vlist)
-    hipLaunchKernelGGL(dgq_vertex_list_kernel<P>, dim3(static_cast<unsigned>((m->Nv + 255) / 256)), dim3(256), 0,
-                       s, u, cand, m->d_vtx_ptr, m->d_vtx_ent, m->Nv, vt, ms, vcount, vlist);
+    hipLaunchKernelGGL(dgq_vertex_list_kernel<P>, dim3(static_cast<unsigned>((m->Nv + 255) / 256), nvar),
+                       dim3(256), 0, s, u, cand, m->d_vtx_ptr, m->d_vtx_ent, m->Nv, vt, ms, vcount, vlist,
+                       m->E * m->nloc);
   else
-    hipLaunchKernelGGL(dgq_vertex_kernel<P>, dim3(static_cast<unsigned>(nb)), dim3(256), 0, s, u, cand,
-                       m->d_vtx_ptr, m->d_vtx_ent, m->Nv, nb, vt, ms);
+    hipLaunchKernelGGL(dgq_vertex_kernel<P>, dim3(static_cast<unsigned>(nb), nvar), dim3(256), 0, s, u, cand,
+                       m->d_vtx_ptr, m->d_vtx_ent, m->Nv, nb, vt, ms, m->E * m->nloc);
 }
 
 cvw_status dgquad_candidates(const cvw_mesh* m, const cvw_params* prm, const float* u, float* cand,
-                             hipStream_t s, const uint32_t* vcount, const int32_t* vlist) {
+                             hipStream_t s, const uint32_t* vcount, const int32_t* vlist, int nvar) {
   const MethodScalars ms = make_scalars(prm);
   switch (m->degree) {
-    case 1: launch_vertex<1>(m, ms, u, cand, vcount, vlist, s); break;
-    case 2: launch_vertex<2>(m, ms, u, cand, vcount, vlist, s); break;
-    case 3: launch_vertex<3>(m, ms, u, cand, vcount, vlist, s); break;
+    case 1: launch_vertex<1>(m, ms, u, cand, vcount, vlist, nvar, s); break;
+    case 2: launch_vertex<2>(m, ms, u, cand, vcount, vlist, nvar, s); break;
+    case 3: launch_vertex<3>(m, ms, u, cand, vcount, vlist, nvar, s); break;
     default: set_error("degree not supported on the GPU path"); return CVW_EUNSUPPORTED;
   }
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;

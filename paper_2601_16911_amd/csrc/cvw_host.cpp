@@ -2412,7 +2412,7 @@ cvw_status cvw_limit(const cvw_mesh* m, const cvw_params* prm, const void* u, vo
     if ((st = tri_eval(m, prm, MODE_SENSOR, uf, nullptr, nullptr, gam, nullptr, cand, w.status, 0.f, 0.f, 0.f, s)) !=
         CVW_OK)
       return st;
-    const bool all = threshold > 1.0 && (prm->sensor != CVW_SENSOR_FIXED || prm->fixed_gamma < threshold);
+    const bool all = limit_all(prm, threshold);
     if (!all) {
       if (u_out != u &&
           hipMemcpyAsync(u_out, u, static_cast<size_t>(m->E) * m->nloc * nv * sizeof(float), hipMemcpyDeviceToDevice,
@@ -2423,15 +2423,16 @@ cvw_status cvw_limit(const cvw_mesh* m, const cvw_params* prm, const void* u, vo
     }
     return tri_limit(m, prm, uf, static_cast<float*>(u_out), cand, count, all ? nullptr : list, s);
   }
-  // the sensor field's vertex candidates (the other variables' follow inside
-  // the limiter, where they are needed; every candidate is taken from the
-  // state before the reconstruction writes, so u_out may be u)
-  if ((st = dgquad_candidates(m, prm, uf, cand, s)) != CVW_OK) return st;
   // sensor values of the sensor field (variable 0): the fused pass where it
-  // applies (the values of cvw_sensor), else the cell pass on the candidates
-  if (use_tile(m, prm)) {
+  // applies (the values of cvw_sensor), else the cell pass on the vertex
+  // candidates.  The other candidates follow inside the limiter, where they
+  // are needed; every candidate is taken from the state before the
+  // reconstruction writes, so u_out may be u.
+  const bool tile = use_tile(m, prm);
+  if (tile) {
     if ((st = dgquad_sensor_tile(m, prm, uf, gam, s)) != CVW_OK) return st;
-  } else if ((st = dgquad_eval(m, prm, MODE_SENSOR, uf, nullptr, nullptr, gam, nullptr, cand, w.status, 0.f, 0.f,
+  } else if ((st = dgquad_candidates(m, prm, uf, cand, s)) != CVW_OK ||
+             (st = dgquad_eval(m, prm, MODE_SENSOR, uf, nullptr, nullptr, gam, nullptr, cand, w.status, 0.f, 0.f,
                                0.f, s)) != CVW_OK) {
     return st;
   }
@@ -2442,8 +2443,8 @@ cvw_status cvw_limit(const cvw_mesh* m, const cvw_params* prm, const void* u, vo
     ln.xi[i] = x[i];
     ln.w[i] = wq[i];
   }
-  return dgquad_limit(m, prm, uf, static_cast<float*>(u_out), cand, gam, ln, threshold, count, list, vflag, vlist,
-                      s);
+  return dgquad_limit(m, prm, uf, static_cast<float*>(u_out), cand, tile ? 0 : 1, gam, ln, threshold, count, list,
+                      vflag, vlist, s);
 }
 
 cvw_status cvw_positivity(const cvw_mesh* m, const cvw_params* prm, const void* u, void* u_out, double eps0,

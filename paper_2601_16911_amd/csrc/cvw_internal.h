@@ -427,18 +427,21 @@ MethodScalars make_scalars(const cvw_params* prm);
 int n_var(const cvw_mesh* m, int flux);   // conserved variables: 1, or dim + 2 for the Euler equations
 
 // kernel launchers (cvw_dgquad.hip)
+// vertex candidates of nvar variables (u [nvar][E][n_loc] to cand
+// [nvar][Nv][n_k]), at every vertex or at the listed ones
 cvw_status dgquad_candidates(const cvw_mesh* m, const cvw_params* prm, const float* u, float* cand,
-                             hipStream_t s, const uint32_t* vcount = nullptr, const int32_t* vlist = nullptr);
+                             hipStream_t s, const uint32_t* vcount = nullptr, const int32_t* vlist = nullptr,
+                             int nvar = 1);
 cvw_status dgquad_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const float* u, const float* u0,
                        float* out, float* gamma, float* alpha, const float* cand, uint32_t* status,
                        float dt, float a0, float b0, hipStream_t s, const float* gamma_in = nullptr);
-// HWENO limiter on DG quadrilaterals (cvw_dgquad.hip): cand holds the vertex
-// candidates of every variable, [n_var][Nv][n_k], variable 0 already
+// HWENO limiter on DG quadrilaterals (cvw_limit.hip): cand takes the vertex
+// candidates of every variable, [n_var][Nv][n_k], those below v0 already
 // computed; gamma the sensor values; count (two words), list (E entries),
 // vflag (Nv bytes) and vlist (Nv entries) are scratch for the selected cells
 // and their vertices
 cvw_status dgquad_limit(const cvw_mesh* m, const cvw_params* prm, const float* u, float* out, float* cand,
-                        const float* gamma, const LimitNodes& ln, double threshold, uint32_t* count,
+                        int v0, const float* gamma, const LimitNodes& ln, double threshold, uint32_t* count,
                         int32_t* list, uint8_t* vflag, int32_t* vlist, hipStream_t s);
 // fused sensor pass of a structured periodic DG quadrilateral grid: gamma_e
 // of every cell from the sensor field (variable 0 of u) (cvw_dgsensor.hip)

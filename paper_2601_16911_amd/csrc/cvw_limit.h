@@ -11,6 +11,10 @@ namespace cvw {
 cvw_status limit_select(const float* gamma, int64_t E, double threshold, uint32_t* count, int32_t* list,
                         hipStream_t s);
 
+// whether the threshold selects every cell: the plain sensor gives gamma_e <= 1
+// (a fixed gamma must be below it)
+bool limit_all(const cvw_params* prm, double threshold);
+
 // HWENO limiter on DG triangles (cvw_tri.hip): cand holds every variable's
 // vertex candidates [n_var][Nv][n_k]; list == nullptr: every cell
 cvw_status tri_limit(const cvw_mesh* m, const cvw_params* prm, const float* u, float* out, const float* cand,

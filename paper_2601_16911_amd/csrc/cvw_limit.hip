@@ -106,42 +106,80 @@ __device__ __forceinline__ void append_selected(bool sel, int64_t id, uint32_t* 
   if (sel) list[bbase + wbase[wave] + below] = static_cast<int32_t>(id);
 }
 
-// Cells to reconstruct: list[0 .. count[0]) (any order: every cell's result
-// is its own).
-__global__ __launch_bounds__(1024) void dgq_limit_select_kernel(const float* __restrict__ gamma, int64_t E,
-                                                                double threshold, uint32_t* __restrict__ count,
-                                                                int32_t* __restrict__ list) {
-  const int64_t e = blockIdx.x * 1024LL + threadIdx.x;
-  append_selected(e < E && static_cast<double>(gamma[e]) < threshold, e, count, list);
+// Block b (1024 threads) of the copy of the cells that are not reconstructed
+// from u to out: chunks of C floats of a cell's row, two per thread
+template <int P>
+__device__ __forceinline__ void copy_rest(const float* __restrict__ u, float* __restrict__ out,
+                                          const float* __restrict__ gamma, double threshold, int64_t E, int nv,
+                                          int64_t b) {
+  constexpr int NLOC = (P + 1) * (P + 1), C = P == 2 ? 3 : 4, CR = NLOC / C;
+  float x[2][C];
+  bool on[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int64_t i = (b * 2 + j) * 1024 + threadIdx.x;
+    on[j] = i < E * nv * CR;
+    if (on[j]) {
+      int64_t e = i / CR;
+#pragma unroll
+      for (int v = 1; v < 4; ++v) e -= e >= E ? E : 0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) x[j][c] = u[i * C + c];
+      on[j] = !(static_cast<double>(gamma[e]) < threshold);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    if (on[j])
+#pragma unroll
+      for (int c = 0; c < C; ++c) out[((b * 2 + j) * 1024 + threadIdx.x) * C + c] = x[j][c];
 }
 
-// Vertices of the selected cells: vlist[0 .. count[1]).
-__global__ __launch_bounds__(1024) void dgq_limit_select_vertices_kernel(const uint8_t* __restrict__ vflag,
-                                                                         int64_t Nv, uint32_t* __restrict__ count,
-                                                                         int32_t* __restrict__ vlist) {
+// What a list holds: the cells below the threshold, the same with their
+// vertices' flags set, or the flagged vertices.
+enum LimitList { LIST_CELLS, LIST_CELLS_MARK, LIST_VERTICES };
+
+// list[0 .. *count): cells to reconstruct, or vertices of them (any order:
+// each one's result is its own).  P > 0: the blocks from nsel on copy the
+// other cells of the degree-P quadrilaterals (bound by memory, the selection
+// by latency).  Flags are plain byte stores and a second list: setting them
+// with atomics and listing a vertex when first set took 35 us (512^2 cells).
+template <int LIST, int P>
+__global__ __launch_bounds__(1024) void limit_list_kernel(const float* __restrict__ gamma, int64_t E,
+                                                          double threshold, uint32_t* __restrict__ count,
+                                                          int32_t* __restrict__ list,
+                                                          const int32_t* __restrict__ cell_vtx,
+                                                          uint8_t* __restrict__ vflag, int64_t Nv, int64_t nsel,
+                                                          const float* __restrict__ u, float* __restrict__ out,
+                                                          int nv) {
+  if constexpr (P > 0) {
+    if (blockIdx.x >= nsel) {                      // the whole block
+      copy_rest<P>(u, out, gamma, threshold, E, nv, blockIdx.x - nsel);
+      return;
+    }
+  }
   const int64_t i = blockIdx.x * 1024LL + threadIdx.x;
-  append_selected(i < Nv && vflag[i] != 0, i, count + 1, vlist);
+  bool sel;
+  if constexpr (LIST == LIST_VERTICES) sel = i < Nv && vflag[i] != 0;
+  else sel = i < E && static_cast<double>(gamma[i]) < threshold;
+  append_selected(sel, i, count, list);
+  if constexpr (LIST == LIST_CELLS_MARK) {
+    if (sel)
+#pragma unroll
+      for (int l = 0; l < 4; ++l) vflag[cell_vtx[i * 4 + l]] = 1;
+  }
 }
 
 __global__ void dgq_limit_clear_kernel(uint32_t* __restrict__ count) {
   if (threadIdx.x < 2) count[threadIdx.x] = 0u;
 }
 
-__global__ __launch_bounds__(256) void dgq_limit_clear_flags_kernel(uint8_t* __restrict__ vflag, int64_t Nv) {
+// both counts and the vertex flags, four to a word (nw words)
+__global__ __launch_bounds__(256) void limit_clear_flags_kernel(uint32_t* __restrict__ count,
+                                                                uint32_t* __restrict__ vflag, int64_t nw) {
   const int64_t i = blockIdx.x * 256LL + threadIdx.x;
-  if (i < Nv) vflag[i] = 0;
-}
-
-// flags the vertices of the listed cells (their candidates are needed)
-__global__ __launch_bounds__(256) void dgq_limit_mark_kernel(const uint32_t* __restrict__ count,
-                                                             const int32_t* __restrict__ list,
-                                                             const int32_t* __restrict__ cell_vtx,
-                                                             uint8_t* __restrict__ vflag, int64_t E) {
-  const int64_t k = blockIdx.x * 256LL + threadIdx.x;
-  if (k >= static_cast<int64_t>(*count) || k >= E) return;
-  const int64_t e = list[k];
-#pragma unroll
-  for (int l = 0; l < 4; ++l) vflag[cell_vtx[e * 4 + l]] = 1;
+  if (i < 2) count[i] = 0u;
+  if (i < nw) vflag[i] = 0u;
 }
 
 // One thread per (listed cell, variable) (the grid covers every cell; threads
@@ -269,53 +307,63 @@ __global__ __launch_bounds__(256) void dgq_limit_kernel(const float* __restrict_
   }
 }
 
+template <int LIST>
+static void launch_list(int P, const float* gamma, int64_t E, double threshold, uint32_t* count, int32_t* list,
+                        const int32_t* cell_vtx, uint8_t* vflag, int64_t Nv, const float* u, float* out, int nv,
+                        hipStream_t s) {
+  const int64_t nsel = ((LIST == LIST_VERTICES ? Nv : E) + 1023) / 1024;
+  const int64_t chunks = E * nv * (P == 0 ? 0 : (P == 1 ? 1 : P + 1));
+  const dim3 g(static_cast<unsigned>(nsel + (chunks + 2047) / 2048)), b(1024);
+  auto kern = P == 0 ? limit_list_kernel<LIST, 0>
+                     : (P == 1 ? limit_list_kernel<LIST, 1>
+                               : (P == 2 ? limit_list_kernel<LIST, 2> : limit_list_kernel<LIST, 3>));
+  hipLaunchKernelGGL(kern, g, b, 0, s, gamma, E, threshold, count, list, cell_vtx, vflag, Nv, nsel, u, out, nv);
+}
+
 cvw_status limit_select(const float* gamma, int64_t E, double threshold, uint32_t* count, int32_t* list,
                         hipStream_t s) {
   hipLaunchKernelGGL(dgq_limit_clear_kernel, dim3(1), dim3(64), 0, s, count);
-  hipLaunchKernelGGL(dgq_limit_select_kernel, dim3(static_cast<unsigned>((E + 1023) / 1024)), dim3(1024), 0, s, gamma,
-                     E, threshold, count, list);
+  launch_list<LIST_CELLS>(0, gamma, E, threshold, count, list, nullptr, nullptr, 0, nullptr, nullptr, 0, s);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 
+bool limit_all(const cvw_params* prm, double threshold) {
+  return threshold > 1.0 && (prm->sensor != CVW_SENSOR_FIXED || prm->fixed_gamma < threshold);
+}
+
+// Few launches, each with enough to do: the flags and counts in one clear, the
+// state copy beside the vertex list (23 us, the copy alone 28), the candidates
+// of all variables in one pass over the listed vertices (12 us against 14 for
+// the sensor field everywhere and 23 for the others one after another).  512^2
+// Q3 Euler 109 -> 76 us, 300x310 Q2 53 -> 32, 33x40 Q3 59 -> 38.
 cvw_status dgquad_limit(const cvw_mesh* m, const cvw_params* prm, const float* u, float* out, float* cand,
-                        const float* gamma, const LimitNodes& ln, double threshold, uint32_t* count,
+                        int v0, const float* gamma, const LimitNodes& ln, double threshold, uint32_t* count,
                         int32_t* list, uint8_t* vflag, int32_t* vlist, hipStream_t s) {
   const MethodScalars ms = make_scalars(prm);
-  const dim3 g(static_cast<unsigned>((m->E + 255) / 256)), b(256);
+  const dim3 b(256);
   const bool sys = prm->flux == CVW_EULER;
   const int nv = sys ? 4 : 1;
   const dim3 gv(static_cast<unsigned>((m->E * nv + 255) / 256));
+  const float* uv0 = u + static_cast<int64_t>(v0) * m->E * m->nloc;
+  float* cv0 = cand + static_cast<int64_t>(v0) * m->Nv * m->nk;
   cvw_status st;
-  // the plain sensor gives gamma_e <= 1: a threshold above 1 (and above a
-  // fixed gamma) selects every cell, which are then taken in order without a
-  // list, and every vertex needs the candidates of every variable
-  if (threshold > 1.0 && (prm->sensor != CVW_SENSOR_FIXED || prm->fixed_gamma < threshold)) {
+  if (limit_all(prm, threshold)) {
+    // every cell in order, without a list; every vertex needs the candidates of every variable
     list = nullptr;
-    for (int v = 1; v < nv; ++v)
-      if ((st = dgquad_candidates(m, prm, u + static_cast<int64_t>(v) * m->E * m->nloc,
-                                  cand + static_cast<int64_t>(v) * m->Nv * m->nk, s)) != CVW_OK)
-        return st;
+    if (v0 < nv && (st = dgquad_candidates(m, prm, uv0, cv0, s, nullptr, nullptr, nv - v0)) != CVW_OK) return st;
   } else {
-    if (out != u &&
-        hipMemcpyAsync(out, u, static_cast<size_t>(m->E) * m->nloc * nv * sizeof(float), hipMemcpyDeviceToDevice,
-                       s) != hipSuccess) {
-      set_error("state copy failed"); return CVW_EDEVICE;
-    }
-    hipLaunchKernelGGL(dgq_limit_clear_kernel, dim3(1), dim3(64), 0, s, count);
-    hipLaunchKernelGGL(dgq_limit_select_kernel, dim3(static_cast<unsigned>((m->E + 1023) / 1024)), dim3(1024), 0, s,
-                       gamma, m->E, threshold, count, list);
-    if (nv > 1) {
-      // the other variables' candidates only at the vertices of selected cells
-      hipLaunchKernelGGL(dgq_limit_clear_flags_kernel, dim3(static_cast<unsigned>((m->Nv + 255) / 256)), b, 0, s,
-                         vflag, m->Nv);
-      hipLaunchKernelGGL(dgq_limit_mark_kernel, g, b, 0, s, count, list, m->d_cell_vtx, vflag, m->E);
-      hipLaunchKernelGGL(dgq_limit_select_vertices_kernel, dim3(static_cast<unsigned>((m->Nv + 1023) / 1024)),
-                         dim3(1024), 0, s, vflag, m->Nv, count, vlist);
-      for (int v = 1; v < nv; ++v)
-        if ((st = dgquad_candidates(m, prm, u + static_cast<int64_t>(v) * m->E * m->nloc,
-                                    cand + static_cast<int64_t>(v) * m->Nv * m->nk, s, count + 1, vlist)) !=
-            CVW_OK)
-          return st;
+    const int pc = out != u ? m->degree : 0;
+    if (v0 < nv) {
+      // the candidates of the variables from v0 on, at the vertices of the selected cells
+      const int64_t nw = (m->Nv + 3) / 4;
+      hipLaunchKernelGGL(limit_clear_flags_kernel, dim3(static_cast<unsigned>((nw + 255) / 256)), b, 0, s, count,
+                         reinterpret_cast<uint32_t*>(vflag), nw);
+      launch_list<LIST_CELLS_MARK>(0, gamma, m->E, threshold, count, list, m->d_cell_vtx, vflag, m->Nv, u, out, nv, s);
+      launch_list<LIST_VERTICES>(pc, gamma, m->E, threshold, count + 1, vlist, nullptr, vflag, m->Nv, u, out, nv, s);
+      if ((st = dgquad_candidates(m, prm, uv0, cv0, s, count + 1, vlist, nv - v0)) != CVW_OK) return st;
+    } else {
+      hipLaunchKernelGGL(dgq_limit_clear_kernel, dim3(1), dim3(64), 0, s, count);
+      launch_list<LIST_CELLS>(pc, gamma, m->E, threshold, count, list, nullptr, nullptr, 0, u, out, nv, s);
     }
   }
 #define CVW_LIMIT_LAUNCH(P)                                                                                        \
