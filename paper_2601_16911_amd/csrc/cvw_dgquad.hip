@@ -1179,8 +1179,7 @@ __global__ __launch_bounds__(256) void dgq_feat_kernel(const float* __restrict__
     uint32_t w[4];
 #pragma unroll
     for (int h = 0; h < 4; ++h)
-      w[h] = static_cast<uint32_t>(bf16_bits(f[8 * q + 2 * h])) |
-             (static_cast<uint32_t>(bf16_bits(f[8 * q + 2 * h + 1])) << 16);
+      w[h] = bf16_pair(f[8 * q + 2 * h], f[8 * q + 2 * h + 1]);
     dst[q] = make_uint4(w[0], w[1], w[2], w[3]);
   }
 }

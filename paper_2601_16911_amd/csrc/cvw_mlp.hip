@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void mlp_infer_kernel(const uint16_t* __restri
           const uint16_t h = static_cast<uint16_t>((w[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
           const float x = bf16_value(h);
           const int k = 16 * kb + 8 * g + i;
-          outside = outside || !(x >= slo[k] && x <= shi[k]);
+          outside |= !((x >= slo[k]) & (x <= shi[k]));
         }
       }
     }
@@ -161,13 +161,14 @@ __global__ __launch_bounds__(256) void mlp_infer_kernel(const uint16_t* __restri
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
-        uint16_t h[8];
+        u32x4 h;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int v = 8 * kb + i;
-          h[i] = bf16_bits(gelu(C1[st][v] + sb1[32 * st + acc_row(v, g)]));
+        for (int i = 0; i < 4; ++i) {
+          const int v = 8 * kb + 2 * i;
+          h[i] = bf16_pair(gelu(C1[st][v] + sb1[32 * st + acc_row(v, g)]),
+                           gelu(C1[st][v + 1] + sb1[32 * st + acc_row(v + 1, g)]));
         }
-        B2[st][kb] = pack8(h);
+        B2[st][kb] = __builtin_bit_cast(bf16x8, h);
       }
     float z = 0.0f;
 #pragma unroll
@@ -179,9 +180,11 @@ __global__ __launch_bounds__(256) void mlp_infer_kernel(const uint16_t* __restri
         for (int kb = 0; kb < 2; ++kb)
           C2 = mma(__builtin_bit_cast(bf16x8, sA[6 + 4 * ht + 2 * st + kb][lane]), B2[st][kb], C2);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < 16; v += 2) {
         const int r = 32 * ht + acc_row(v, g);
-        z = fmaf(sw3[r], bf16_value(bf16_bits(gelu(C2[v] + sb2[r]))), z);
+        const uint32_t h = bf16_pair(gelu(C2[v] + sb2[r]), gelu(C2[v + 1] + sb2[r + 1]));
+        z = fmaf(sw3[r], __uint_as_float(h << 16), z);
+        z = fmaf(sw3[r + 1], __uint_as_float(h & 0xFFFF0000u), z);
       }
     }
     z += __shfl_xor(z, 32);
