@@ -320,7 +320,8 @@ cvw_status cvw_residual_noalloc(const cvw_mesh* mesh, const cvw_params* prm, con
  * segments, M_ref |det J| on triangles); CG the consistent global mass,
  * inverted on the device by preconditioned conjugate gradients (lumped-mass
  * preconditioner, relative tolerance 2e-7 in float32 and 1e-14 in float64,
- * at most 64 / 160 iterations; no host synchronisation).  u_n is not read
+ * at most 64 / 160 iterations, fewer where the mesh's mass condition bounds
+ * them; no host synchronisation), on segments of degree <= 4 directly.  u_n is not read
  * when a0 == 0; u_out may alias u_n (each entry of u_n is read only by the
  * thread that overwrites it) but must not alias u_stage or cand.  Meshes:
  * every mesh with a GPU path (DG quads and triangles, CG quads, segments). */
@@ -435,8 +436,8 @@ cvw_status cvw_mlp_train_step(cvw_mlp* mlp, const void* feat, const void* target
 /* ---------------------------------------------------------------------------
  * Batched time stepping of many independent problems (an ensemble of DG
  * meshes, Sec. 2 and Sec. 5 applied per instance): every SSP-RK3 stage of all
- * instances runs as one sensor pass per degree and one cell pass per
- * (degree, flux), captured once into a HIP graph that is replayed per step.
+ * instances runs as one sensor (or vertex) pass and one cell pass, captured
+ * once into a HIP graph that is replayed per step.
  * The sensor pass is the fused one of cvw_sensor for instances with the plain
  * sensor on a structured periodic grid (gamma of the stage in the workspace,
  * read by the cell pass), else the vertex pass (CVW_SENSOR_PATH=twopass when

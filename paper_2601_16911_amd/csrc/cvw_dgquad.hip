@@ -1275,6 +1275,17 @@ __device__ __forceinline__ void batch_vertex_list(const BatchInst* __restrict__ 
   }
 }
 
+// one list by itself, a stride walk
+template <int P>
+__global__ __launch_bounds__(256) void batch_vertex_one_kernel(const BatchInst* __restrict__ inst,
+                                                               const int2* __restrict__ items, int n, int stage) {
+  for (int it = blockIdx.x; it < n; it += gridDim.x) {
+    const int2 w = items[it];
+    const BatchInst& I = inst[w.x];
+    dgq_vertex_body<P>(I.u_in[stage], I.cand, I.vptr, I.vent, I.Nv, w.y, I.vt, I.ms);
+  }
+}
+
 __global__ __launch_bounds__(256) void batch_vertex_kernel(const BatchInst* __restrict__ inst, BatchLists L,
                                                            int stage) {
   int k = 0, first = 0;
@@ -1316,6 +1327,31 @@ __device__ __forceinline__ void batch_eval_flux(const BatchInst* __restrict__ in
   }
 }
 
+// one list by itself, a stride walk
+template <int P, int FLUX>
+__global__ __launch_bounds__(256) void batch_eval_one_kernel(const BatchInst* __restrict__ inst,
+                                                             const int2* __restrict__ items, int n_items,
+                                                             const TensorTables* __restrict__ tabs,
+                                                             const LaneRec* __restrict__ lanes, int stage) {
+  __shared__ LaneRec sl[16];
+  load_lane_tables(lanes + 16 * P, sl);
+  __syncthreads();
+  const float A0[3] = {0.0f, 0.75f, 1.0f / 3.0f}, B0[3] = {1.0f, 0.25f, 2.0f / 3.0f};
+  const float a0 = A0[stage], b0 = B0[stage];
+  const TensorTables& tab = tabs[P];
+  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const int2 w = items[it];
+    const BatchInst& I = inst[w.x];
+    if constexpr (P == 1)
+      dgq_eval_body_p1<FLUX>(I.u_in[stage], I.u, I.u_out[stage], nullptr, nullptr, I.cand, I.cell_vtx, I.nbr,
+                             reinterpret_cast<const LaneRec1*>(sl), I.E, w.y, I.g, I.ms, MODE_STAGE, I.dt, a0, b0,
+                             I.status, I.gam);
+    else
+      dgq_eval_body<P, FLUX>(I.u_in[stage], I.u, I.u_out[stage], nullptr, nullptr, I.cand, I.cell_vtx, I.nbr, sl,
+                             tab, I.E, w.y, I.g, I.ms, MODE_STAGE, I.dt, a0, b0, I.status, I.gam);
+  }
+}
+
 __global__ __launch_bounds__(256) void batch_eval_kernel(const BatchInst* __restrict__ inst, BatchLists L,
                                                          const TensorTables* __restrict__ tabs,
                                                          const LaneRec* __restrict__ lanes, int stage) {
@@ -1334,13 +1370,32 @@ __global__ __launch_bounds__(256) void batch_eval_kernel(const BatchInst* __rest
 
 cvw_status batch_vertex_pass(const BatchInst* inst, const BatchLists& L, int stage, hipStream_t s) {
   if (L.count == 0) return CVW_OK;
+  if (L.count == 1) {
+    const BatchList& l = L.l[0];
+    auto kern = l.P == 1 ? batch_vertex_one_kernel<1> : (l.P == 2 ? batch_vertex_one_kernel<2> : batch_vertex_one_kernel<3>);
+    hipLaunchKernelGGL(kern, dim3(l.end), dim3(256), 0, s, inst, l.items, l.n, stage);
+    return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
+  }
   hipLaunchKernelGGL(batch_vertex_kernel, dim3(L.l[L.count - 1].end), dim3(256), 0, s, inst, L, stage);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
+}
+
+template <int P>
+static auto eval_one(int flux) {
+  return flux == CVW_ADVECT_CONST ? batch_eval_one_kernel<P, CVW_ADVECT_CONST>
+                                  : (flux == CVW_BURGERS ? batch_eval_one_kernel<P, CVW_BURGERS>
+                                                         : batch_eval_one_kernel<P, CVW_KPP>);
 }
 
 cvw_status batch_eval_pass(const BatchInst* inst, const BatchLists& L, const TensorTables* tabs,
                            const LaneRec* lanes, int stage, hipStream_t s) {
   if (L.count == 0) return CVW_OK;
+  if (L.count == 1) {
+    const BatchList& l = L.l[0];
+    auto kern = l.P == 1 ? eval_one<1>(l.flux) : (l.P == 2 ? eval_one<2>(l.flux) : eval_one<3>(l.flux));
+    hipLaunchKernelGGL(kern, dim3(l.end), dim3(256), 0, s, inst, l.items, l.n, tabs, lanes, stage);
+    return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
+  }
   hipLaunchKernelGGL(batch_eval_kernel, dim3(L.l[L.count - 1].end), dim3(256), 0, s, inst, L, tabs, lanes, stage);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }

@@ -523,6 +523,17 @@ __device__ __forceinline__ void batch_sensor_list(const BatchInst* __restrict__ 
   }
 }
 
+// one list by itself, a stride walk
+template <int P>
+__global__ __launch_bounds__(256, 4) void batch_sensor_one_kernel(const BatchInst* __restrict__ inst,
+                                                                  const int2* __restrict__ items, int n, int stage) {
+  for (int it = blockIdx.x; it < n; it += gridDim.x) {
+    const int2 w = items[it];
+    const BatchInst& I = inst[w.x];
+    sensor_tile_body<P>(I.u_in[stage], I.gam, I.sa, I.ms, w.y, TILE_ALL, nullptr, nullptr, nullptr);
+  }
+}
+
 __global__ __launch_bounds__(256, 4) void batch_sensor_kernel(const BatchInst* __restrict__ inst, BatchLists L,
                                                               int stage) {
   int k = 0, first = 0;
@@ -631,6 +642,12 @@ cvw_status dgquad_sensor_tile(const cvw_mesh* m, const cvw_params* prm, const fl
 
 cvw_status batch_sensor_pass(const BatchInst* inst, const BatchLists& L, int stage, hipStream_t s) {
   if (L.count == 0) return CVW_OK;
+  if (L.count == 1) {
+    const BatchList& l = L.l[0];
+    auto kern = l.P == 1 ? batch_sensor_one_kernel<1> : (l.P == 2 ? batch_sensor_one_kernel<2> : batch_sensor_one_kernel<3>);
+    hipLaunchKernelGGL(kern, dim3(l.end), dim3(256), 0, s, inst, l.items, l.n, stage);
+    return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
+  }
   hipLaunchKernelGGL(batch_sensor_kernel, dim3(L.l[L.count - 1].end), dim3(256), 0, s, inst, L, stage);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }

@@ -2781,37 +2781,62 @@ static void batch_free(cvw_batch* b) {
   delete b;
 }
 
-// The lists of a pass with their share of the launch's blocks.  By default one
-// run length for the whole pass, chosen for at most BATCH_BLOCKS blocks: a few
-// resident rounds (a step of 24 meshes: 2048 blocks 342 us, 4096 308, 8192 310,
-// one item per block 359).
-constexpr int64_t BATCH_BLOCKS = 4096;
-static BatchLists batch_lists(const cvw_batch* b, const cvw_batch::Lists& lists) {
+// By default a launch has at most BATCH_BLOCKS blocks: a few resident rounds (a
+// step of 24 meshes: 2048 blocks 342 us, 4096 308, 8192 310, one item per block
+// 359).  A list of BATCH_ALONE items or more fills the chip by itself and runs
+// in a kernel of its own, whose registers let six wavefronts per SIMD share it
+// instead of five (64 meshes, 41.6 M DOFs: all lists together 1.92 ms per
+// step, from 16,384 items on alone 1.65, from 4,096 on 1.66); below, a launch
+// of its own leaves the chip idle at its end (16 meshes: alone from 8,192 items
+// on 199 us, from 16,384 on 187).
+constexpr int64_t BATCH_BLOCKS = 4096, BATCH_ALONE = 16384;
+
+static void add_list(BatchLists& L, const cvw_batch::List& l, int run) {
+  BatchList& o = L.l[L.count];
+  o.items = l.d;
+  o.n = l.n;
+  o.run = run;
+  o.end = (L.count ? L.l[L.count - 1].end : 0) + ((l.n - 1) / run + 8) / 8 * 8;
+  o.P = l.P;
+  o.flux = l.flux;
+  ++L.count;
+}
+
+// The launches of a pass: each list of BATCH_ALONE items or more by itself,
+// the others together.
+template <typename LAUNCH>
+static cvw_status batch_pass(const cvw_batch* b, const cvw_batch::Lists& lists, LAUNCH launch) {
   static_assert(MAXP * 3 <= BatchLists::MAX, "a list per degree and scalar flux");
-  BatchLists L;
   int64_t items = 0;
-  for (const auto& l : lists) items += l.n;
-  const int run = static_cast<int>((items + BATCH_BLOCKS - 1) / BATCH_BLOCKS);
-  int end = 0;
+  for (const auto& l : lists)
+    if (l.n < BATCH_ALONE) items += l.n;
+  const int shared_run = static_cast<int>((items + BATCH_BLOCKS - 1) / BATCH_BLOCKS);
+  BatchLists shared;
   for (const auto& l : lists) {
-    BatchList& o = L.l[L.count++];
-    o.items = l.d;
-    o.n = l.n;
-    o.run = b->grid > 0 ? (l.n - 1) / std::min(b->grid, l.n) + 1 : run;
-    end += ((l.n - 1) / o.run + 8) / 8 * 8;
-    o.end = end;
-    o.P = l.P;
-    o.flux = l.flux;
+    const bool alone = l.n >= BATCH_ALONE;
+    const int run = b->grid > 0 ? (l.n - 1) / std::min(b->grid, l.n) + 1
+                                : (alone ? static_cast<int>((l.n + BATCH_BLOCKS - 1) / BATCH_BLOCKS) : shared_run);
+    if (!alone) {
+      add_list(shared, l, run);
+      continue;
+    }
+    BatchLists own;
+    add_list(own, l, run);
+    const cvw_status st = launch(own);
+    if (st != CVW_OK) return st;
   }
-  return L;
+  return launch(shared);
 }
 
 // one pass of every stage kernel on stream s (used eagerly and under capture)
 static cvw_status batch_launch_stage(const cvw_batch* b, int stage, hipStream_t s) {
-  cvw_status st = batch_sensor_pass(b->d_inst, batch_lists(b, b->slists), stage, s);
-  if (st == CVW_OK) st = batch_vertex_pass(b->d_inst, batch_lists(b, b->vlists), stage, s);
+  cvw_status st = batch_pass(b, b->slists, [&](const BatchLists& L) { return batch_sensor_pass(b->d_inst, L, stage, s); });
   if (st == CVW_OK)
-    st = batch_eval_pass(b->d_inst, batch_lists(b, b->elists), b->d_tabs, b->d_lanes, stage, s);
+    st = batch_pass(b, b->vlists, [&](const BatchLists& L) { return batch_vertex_pass(b->d_inst, L, stage, s); });
+  if (st == CVW_OK)
+    st = batch_pass(b, b->elists, [&](const BatchLists& L) {
+      return batch_eval_pass(b->d_inst, L, b->d_tabs, b->d_lanes, stage, s);
+    });
   return st;
 }
 

@@ -483,12 +483,13 @@ cvw_status seghp_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const 
                       const LineStage& lst);
 // Batched DG quadrilateral stage over many meshes.  A pass holds up to 9 work
 // lists, one per degree (cell pass: per degree and flux), of (instance,
-// logical block) items; it is ONE launch, list k taken by the blocks
-// [l[k - 1].end, l[k].end), each walking a run of consecutive items (the
-// blocks of one XCD hold consecutive runs: neighbour rows share its L2).
-// Few of the lists fill the chip by themselves: a step of 16 meshes, 27
-// launches one after another, took 270 us; as 6 launches with one item per
-// block 221 us; with runs (the lane tables are staged once per block) 189 us.
+// logical block) items.  Small lists share one launch, list k taken by the
+// blocks [l[k - 1].end, l[k].end), each walking a run of consecutive items (the
+// blocks of one XCD hold consecutive runs: neighbour rows share its L2); a
+// launch given one list takes the kernel of its degree and flux, a stride walk.
+// A step of 16 meshes, 27 launches one after another, took 270 us; as 6
+// launches with one item per block 221 us; with runs (the lane tables are
+// staged once per block) 187 us.
 struct BatchList {
   const int2* items = nullptr;
   int n = 0;       // items
