@@ -17,16 +17,16 @@
 // Lines: a direct solve at low degree, the same iteration inside one workgroup
 // per variable at high degree.
 #include "cvw_device.h"
+#include "cvw_pcg.h"
 
 #include <algorithm>
 #include <cmath>
 
 namespace cvw {
 
-enum { S_RZ = 0, S_RZ_ODD = 1, S_RZ0 = 2, S_ALPHA = 3, S_BETA = 4, S_DONE = 5, S_TOL2 = 6, S_NOX = 7 };
 constexpr int PCG_THREADS = 256;
 
-__device__ __forceinline__ bool pcg_done(const double* S) { return S[S_DONE] != 0.0; }
+__device__ __forceinline__ bool pcg_writer() { return blockIdx.x == 0 && threadIdx.x == 0; }
 
 // sum of one double per thread over N threads in the order of a halving tree
 // (s = N / 2, ..., 1: thread t adds t + s); the last six levels lie inside the
@@ -91,10 +91,7 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_init_kernel(const float* __re
                                                                double* __restrict__ S, double tol2) {
   __shared__ double sh[PCG_THREADS];
   const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    S[S_DONE] = 0.0;
-    S[S_TOL2] = tol2;
-  }
+  if (pcg_writer()) pcg_setup(S, tol2);
   double d = 0.0;
   if (i < n) {
     float bi = 0.0f;
@@ -108,30 +105,9 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_init_kernel(const float* __re
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// The recurrence at the start of iteration it, from rz = r.z: rz0, beta, done (a
-// zero right-hand side, or the tolerance met); block 0 writes it for the launches
-// behind.  false: done.
-template <bool FIRST>
-__device__ __forceinline__ bool pcg_recur(double rz, double* S, int it, float& beta) {
-  const double b = FIRST ? 0.0 : rz / S[(it & 1) ? S_RZ : S_RZ_ODD];
-  const bool done = FIRST ? !(rz > 0.0) : !(rz > S[S_TOL2] * S[S_RZ0]);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    S[(it & 1) ? S_RZ_ODD : S_RZ] = rz;
-    S[S_BETA] = b;
-    if (FIRST) {
-      S[S_RZ0] = rz;
-      S[S_NOX] = done ? 1.0 : 0.0;
-    }
-    if (done) S[S_DONE] = 1.0;
-  }
-  beta = static_cast<float>(b);
-  return !done;
-}
-
 // p = z + beta p (FIRST: p = z) at the cell's nodes and y = M_e p; the (p+1)^2 Gauss
 // rule integrates phi_i phi_j |det J| exactly (degree 2p + 1 per direction).
-// FUSED: v = r.z from its partials; its recurrence (rz0, done, beta) is written
-// for the launches behind by block 0.
+// FUSED: this launch begins the iteration (r.z from its partials).
 template <int P, bool FIRST, bool FUSED>
 __global__ __launch_bounds__(PCG_THREADS) void pcg_cells_kernel(const float2* __restrict__ pz, float* __restrict__ ycell,
                                                                 const double* __restrict__ rz_part, int nb,
@@ -141,7 +117,7 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_cells_kernel(const float2* __
                                                                 int it) {
   constexpr int N1 = P + 1, NLOC = N1 * N1;
   __shared__ double sh[PCG_THREADS];
-  if (pcg_done(S)) return;
+  if (FUSED ? !pcg_enter(S, it, pcg_writer()) : !pcg_runs(S, it)) return;
   const int64_t e = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x, ec = e < E ? e : E - 1;
   int I[NLOC];
   float2 v[NLOC];
@@ -153,7 +129,7 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_cells_kernel(const float2* __
   float beta = 0.0f;
   if constexpr (FUSED) {
     const double rz = partial_sum(rz_part, nb, sh);
-    if (!pcg_recur<FIRST>(rz, S, it, beta)) return;
+    if (!pcg_begin<FIRST>(rz, S, it, pcg_writer(), beta)) return;
   } else if constexpr (!FIRST) {
     beta = static_cast<float>(S[S_BETA]);
   }
@@ -194,9 +170,9 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_gather_kernel(const float* __
                                                                  const int4* __restrict__ ent4,
                                                                  const int32_t* __restrict__ dptr,
                                                                  const int32_t* __restrict__ dent, int64_t E, int64_t n,
-                                                                 const double* __restrict__ S) {
+                                                                 const double* __restrict__ S, int it) {
   __shared__ double sh[PCG_THREADS];
-  if (pcg_done(S)) return;
+  if (!pcg_runs(S, it)) return;
   const int64_t I = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
   double d = 0.0;
   if (I < n) {
@@ -206,9 +182,9 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_gather_kernel(const float* __
                 y3 = ycell[k.w < 0 ? 0 : k.w];
     float s = 0.0f;
     if (k.x == -2) {
-      for (int it = dptr[I]; it < dptr[I + 1]; ++it) {
-        const int64_t e = dent[it] / NLOC;
-        s += ycell[(dent[it] - e * NLOC) * E + e];
+      for (int c = dptr[I]; c < dptr[I + 1]; ++c) {
+        const int64_t e = dent[c] / NLOC;
+        s += ycell[(dent[c] - e * NLOC) * E + e];
       }
     } else {
       s += y0;
@@ -250,7 +226,7 @@ struct MassBasis {
   float phi[NLOC][NLOC];
 };
 
-// cells and gather in one (FUSED recurrence as in pcg_cells_kernel): Ap_I = sum over
+// cells and gather in one (begins the iteration): Ap_I = sum over
 // the cells sharing I of the row sum_q phi_I(x_q) W_q p_h(x_q); the directions
 // alternate between pz and pz_new, as other DOFs still read the old one
 template <int P, bool FIRST>
@@ -262,10 +238,10 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_apply_kernel(
   constexpr int NLOC = (P + 1) * (P + 1);
   __shared__ double sh[PCG_THREADS];
   __shared__ float sphi[NLOC][NLOC];      // [j][q]
-  if (pcg_done(S)) return;
+  if (!pcg_enter(S, it, pcg_writer())) return;
   const double rz = partial_sum(rz_part, nb, sh);
   float beta;
-  if (!pcg_recur<FIRST>(rz, S, it, beta)) return;
+  if (!pcg_begin<FIRST>(rz, S, it, pcg_writer(), beta)) return;
   if (threadIdx.x < NLOC * NLOC) sphi[threadIdx.x % NLOC][threadIdx.x / NLOC] = (&B.phi[0][0])[threadIdx.x];
   __syncthreads();
   const int64_t I = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
@@ -314,11 +290,11 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_update_kernel(float* __restri
                                                                  double* __restrict__ rz_part, int nb, int64_t n,
                                                                  const double* __restrict__ S, int it) {
   __shared__ double sh[PCG_THREADS];
-  if (pcg_done(S)) return;
+  if (!pcg_runs(S, it)) return;
   const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x, ic = i < n ? i : n - 1;
   const float p = pz[ic].x, xo = FIRST ? 0.0f : x[ic], ro = r[ic], ap = Ap[ic], di = dinv[ic];
   float al;
-  if constexpr (FUSED) al = static_cast<float>(S[(it & 1) ? S_RZ_ODD : S_RZ] / partial_sum(pap_part, nb, sh));
+  if constexpr (FUSED) al = static_cast<float>(S[pcg_rz_word(it)] / partial_sum(pap_part, nb, sh));
   else al = static_cast<float>(S[S_ALPHA]);
   double d = 0.0;
   if (i < n) {
@@ -333,49 +309,44 @@ __global__ __launch_bounds__(PCG_THREADS) void pcg_update_kernel(float* __restri
   if (threadIdx.x == 0) rz_part[blockIdx.x] = s;
 }
 
-// Sum of the block partials and the scalar recurrences (large meshes).
-//   op 0: rz = rz0 = sum (done at once for a zero right-hand side)
-//   op 1: alpha = rz / (p . Ap)
-//   op 2: beta = rz_new / rz, rz = rz_new, done once rz_new <= tol^2 rz0
+// Large meshes, one block: the beginning of iteration `it` (which its other
+// launches then only read), or its alpha = rz / (p . Ap), from the block partials.
+enum { SCALAR_BEGIN, SCALAR_ALPHA };
 __global__ __launch_bounds__(PCG_THREADS) void pcg_scalar_kernel(const double* __restrict__ part, int nb,
-                                                                 double* __restrict__ S, int op) {
+                                                                 double* __restrict__ S, int op, int it) {
   __shared__ double sh[PCG_THREADS];
-  if (pcg_done(S)) return;
+  if (op == SCALAR_BEGIN ? !pcg_enter(S, it, pcg_writer()) : !pcg_runs(S, it)) return;
   const double v = partial_sum(part, nb, sh);
-  if (threadIdx.x != 0) return;
-  if (op == 0) {
-    S[S_RZ] = v;
-    S[S_RZ0] = v;
-    S[S_NOX] = v > 0.0 ? 0.0 : 1.0;
-    if (!(v > 0.0)) S[S_DONE] = 1.0;
-  } else if (op == 1) {
-    S[S_ALPHA] = S[S_RZ] / v;
+  float beta;
+  if (op == SCALAR_ALPHA) {
+    if (pcg_writer()) S[S_ALPHA] = S[pcg_rz_word(it)] / v;
+  } else if (it == 0) {
+    pcg_begin<true>(v, S, it, pcg_writer(), beta);
   } else {
-    S[S_BETA] = v / S[S_RZ];
-    S[S_RZ] = v;
-    if (!(v > S[S_TOL2] * S[S_RZ0])) S[S_DONE] = 1.0;
+    pcg_begin<false>(v, S, it, pcg_writer(), beta);
   }
 }
 
 // u_out = a0 u_n + b0 (u_s - dt x) (no iteration: x = 0).  A solve that has not met
 // its tolerance (nor broken down) when the launch sequence ends sets
-// ST_PCG_STALL in the workspace status word (part: the last partials of r.z when
-// no scalar launch has judged them).
+// ST_PCG_STALL in the workspace status word.  it: the last iteration begun; part:
+// the partials of r.z after it (null: a scalar launch has begun it, so they are
+// judged).
 __global__ __launch_bounds__(PCG_THREADS) void pcg_finish_kernel(const float* __restrict__ us,
                                                                  const float* __restrict__ un,
                                                                  const float* __restrict__ x, float* __restrict__ uo,
                                                                  float a0, float b0, float dt, int64_t n,
-                                                                 const double* __restrict__ S,
+                                                                 const double* __restrict__ S, int it,
                                                                  const double* __restrict__ part, int nb,
                                                                  uint32_t* __restrict__ status) {
   __shared__ double sh[PCG_THREADS];
-  if (blockIdx.x == 0 && !pcg_done(S)) {
+  if (blockIdx.x == 0 && pcg_runs(S, it)) {
     const bool ok = part && !(partial_sum(part, nb, sh) > S[S_TOL2] * S[S_RZ0]);
     if (threadIdx.x == 0 && !ok) atomicOr(status, ST_PCG_STALL);
   }
   const int64_t i = blockIdx.x * static_cast<int64_t>(PCG_THREADS) + threadIdx.x;
   if (i >= n) return;
-  const float xi = S[S_NOX] != 0.0 ? 0.0f : x[i];
+  const float xi = S[pcg_state_word(it)] == PCG_NO_RHS ? 0.0f : x[i];
   const float base = (a0 != 0.0f) ? a0 * un[i] : 0.0f;
   uo[i] = base + b0 * (us[i] - dt * xi);
 }
@@ -621,7 +592,7 @@ static cvw_status quad_pcg(const cvw_mesh* m, const float* rcell, const QuadSolv
   const dim3 g(nb), t(PCG_THREADS);
   hipLaunchKernelGGL(pcg_init_kernel, g, t, 0, s, rcell, m->d_dinv_f, q.r, q.pz, rz, m->d_dof_ptr, m->d_dof_ent, n,
                      q.S, tol * tol);
-  if (!fused) hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, rz, nb, q.S, 0);
+  if (!fused) hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, rz, nb, q.S, SCALAR_BEGIN, 0);
   const int iters = pcg_iterations(m->mass_cond, tol, maxit);
   const bool one = fused && nb <= PCG_APPLY_PARTIALS;
   MassBasis<NLOC> B;
@@ -652,7 +623,7 @@ static cvw_status quad_pcg(const cvw_mesh* m, const float* rcell, const QuadSolv
     };
     auto gather = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, g, t, 0, s, q.y, q.pz, q.Ap, pap, m->d_dof_ent4, m->d_dof_ptr, m->d_dof_ent, m->E, n,
-                         q.S);
+                         q.S, it);
     };
     if (fused) {
       if (it == 0) cells(pcg_cells_kernel<P, true, true>); else cells(pcg_cells_kernel<P, false, true>);
@@ -663,13 +634,14 @@ static cvw_status quad_pcg(const cvw_mesh* m, const float* rcell, const QuadSolv
     if (fused) {
       if (it == 0) update(pcg_update_kernel<true, true>); else update(pcg_update_kernel<false, true>);
     } else {
-      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, pap, nb, q.S, 1);
+      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, pap, nb, q.S, SCALAR_ALPHA, it);
       if (it == 0) update(pcg_update_kernel<true, false>); else update(pcg_update_kernel<false, false>);
-      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, rz, nb, q.S, 2);
+      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), t, 0, s, rz, nb, q.S, SCALAR_BEGIN, it + 1);
     }
   }
   hipLaunchKernelGGL(pcg_finish_kernel, g, t, 0, s, us, un, x, uo, static_cast<float>(a0), static_cast<float>(b0),
-                     static_cast<float>(dt), n, q.S, fused ? rz : nullptr, nb, status);
+                     static_cast<float>(dt), n, q.S, fused ? iters - 1 : iters, fused ? rz : nullptr, nb,
+                     status);
   return hipGetLastError() == hipSuccess ? CVW_OK : CVW_EDEVICE;
 }
 
