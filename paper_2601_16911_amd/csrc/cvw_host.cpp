@@ -2293,10 +2293,28 @@ static cvw_status learned_audit(const cvw_mesh* m, const cvw_params* prm, const 
   return dgquad_audit_finalize(m, w.apart, prm->audit_tol, w.status, w.aout, s);
 }
 
+// Whether a line's candidates come from a vertex pass of their own.  In the cell
+// kernel every vertex is evaluated by both of its cells, which saves a launch
+// (3-4 us) and costs the arithmetic twice: the vertex pass wins where that is
+// dear.  With the general exponents (two pow per cell and vertex), always: DG P4,
+// 8 cells 21.0 us a residual against 21.6 in the cell kernel, 10,000 cells 73
+// against 88, 100,000 cells 609 against 772; P1 11 against 14, 11 and 16 on
+// either way.  Else the one-thread-per-cell kernels never (P3, 1,000,000 cells:
+// 53 against 44) and those of a wavefront per cell on long lines or at high
+// degree: a step of P8 Euler on 3000 cells 110 against 107, on 10,000 cells 251
+// against 257, on 100,000 cells 2091 against 2221; P1 78 / 130 / 1070 there with
+// the cell kernel alone, 83 / 130 / 1013; P12 on 1000 cells 123 on either way,
+// P16 132 against 134 on 100 cells, P32 319 against 328.
+constexpr int64_t LINE_VERTEX_PASS_CELLS = 8192;
+constexpr int LINE_VERTEX_PASS_DEGREE = 16;
+static bool line_vertex_pass(const cvw_mesh* m, const cvw_params* prm) {
+  if (!make_scalars(prm).fast_exp) return true;
+  return seg_hp(m, prm) && (m->E >= LINE_VERTEX_PASS_CELLS || m->degree >= LINE_VERTEX_PASS_DEGREE);
+}
+
 // whether an evaluation goes through the vertex candidates in the workspace
-// (the line kernels form those of a cell's two vertices themselves)
 static bool needs_candidates(const cvw_mesh* m, const cvw_params* prm) {
-  return prm->sensor != CVW_SENSOR_FIXED && m->cell != CVW_SEG;
+  return prm->sensor != CVW_SENSOR_FIXED && (m->cell != CVW_SEG || line_vertex_pass(m, prm));
 }
 
 static cvw_status candidates_any(const cvw_mesh* m, const cvw_params* prm, const void* u, void* cand,
@@ -2349,7 +2367,8 @@ cvw_status cvw_sensor(const cvw_mesh* m, const cvw_params* prm, const void* u, v
                        static_cast<const float*>(gamma));
   }
   if (m->cell == CVW_SEG)
-    return seg_eval(m, prm, MODE_SENSOR, u, nullptr, w.rcell, nullptr, gamma, alpha, w.status, s);
+    return seg_eval(m, prm, MODE_SENSOR, u, needs_candidates(m, prm) ? w.cand : nullptr, w.rcell, nullptr, gamma, alpha,
+                    w.status, s);
   if (m->cell == CVW_TET)
     return tet_eval(m, prm, MODE_SENSOR, static_cast<const float*>(u), nullptr, nullptr, static_cast<float*>(gamma),
                     static_cast<float*>(alpha), static_cast<const float*>(w.cand), w.gam, w.status, 0.f, 0.f, 0.f, s);
@@ -2506,7 +2525,8 @@ cvw_status cvw_residual(const cvw_mesh* m, const cvw_params* prm, const void* u,
   }
   if (prm->sensor == CVW_SENSOR_LEARNED && (st = learned_gamma(m, prm, u, w.cand, w, s)) != CVW_OK) return st;
   if (m->cell == CVW_SEG)
-    return seg_eval(m, prm, MODE_RESIDUAL, u, nullptr, w.rcell, R, gamma_out, nullptr, w.status, s);
+    return seg_eval(m, prm, MODE_RESIDUAL, u, needs_candidates(m, prm) ? w.cand : nullptr, w.rcell, R, gamma_out, nullptr,
+                    w.status, s);
   if (m->cell == CVW_TET)
     return tet_eval(m, prm, MODE_RESIDUAL, static_cast<const float*>(u), nullptr, static_cast<float*>(R),
                     static_cast<float*>(gamma_out), nullptr, static_cast<const float*>(w.cand), w.gam, w.status, 0.f,
@@ -2668,7 +2688,7 @@ cvw_status cvw_step(const cvw_mesh* m, const cvw_params* prm, void* u, double dt
     for (const auto& sg : stages) {
       const bool cand = needs_candidates(m, prm) && !use_tile(m, prm);
       if (cand && (st = candidates_any(m, prm, sg.in, w.cand, s)) != CVW_OK) return st;
-      st = any_stage(m, prm, w, sg.in, m->cell == CVW_SEG ? nullptr : w.cand, u, sg.out, dt, sg.a0, sg.b0, s);
+      st = any_stage(m, prm, w, sg.in, m->cell == CVW_SEG && !cand ? nullptr : w.cand, u, sg.out, dt, sg.a0, sg.b0, s);
       if (st != CVW_OK) return st;
     }
   }
