@@ -101,7 +101,8 @@ __global__ __launch_bounds__(256) void seg_vertex_kernel(const Real* __restrict_
   for (int k = 0; k < P; ++k) cand[i * P + k] = static_cast<Real>(acc[k] / wsum);
 }
 
-template <int P, typename Real, bool CG, int FLUX>
+// OWN: the candidates of the cell's two vertices are formed here, else given
+template <int P, typename Real, bool CG, int FLUX, bool OWN>
 __global__ __launch_bounds__(64) void seg_cell_kernel(const Real* __restrict__ u, const Real* __restrict__ cand,
                                                        const int32_t* __restrict__ cdof,
                                                        const int32_t* __restrict__ cell_vtx,
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(64) void seg_cell_kernel(const Real* __restrict__ u
     for (int l = 0; l < 2; ++l) {
       const int64_t vid = cell_vtx[e * 2 + l];
       Real cv[P];
-      if (cand) {
+      if constexpr (!OWN) {
 #pragma unroll
         for (int k = 0; k < P; ++k) cv[k] = cand[vid * P + k];
       } else {
@@ -388,7 +389,8 @@ static void seg_eval_l(const cvw_mesh* m, const MethodScalars& ms, int mode, con
                        hipStream_t s) {
   const Real* dinv = std::is_same<Real, double>::value ? reinterpret_cast<const Real*>(m->d_dinv_d)
                                                        : reinterpret_cast<const Real*>(m->d_dinv_f);
-  hipLaunchKernelGGL((seg_cell_kernel<P, Real, CG, FLUX>), dim3(nb1(m->E, 64)), dim3(64), 0, s,
+  const auto kern = cand ? seg_cell_kernel<P, Real, CG, FLUX, false> : seg_cell_kernel<P, Real, CG, FLUX, true>;
+  hipLaunchKernelGGL(kern, dim3(nb1(m->E, 64)), dim3(64), 0, s,
                      static_cast<const Real*>(u), static_cast<const Real*>(cand),
                      m->d_cell_dof, m->d_cell_vtx, m->d_line_nb, m->d_hcell, m->d_segt, m->E, ms, mode,
                      static_cast<Real*>(CG ? rcell : R), static_cast<Real*>(gamma), static_cast<Real*>(alpha),

@@ -177,6 +177,8 @@ __global__ __launch_bounds__(64) void hp_vertex_kernel(SegHPArgs A, const double
 }
 
 // ---------------------------------------------------------------------------
+// OWN: the candidates of the cell's two vertices are formed here, else given
+template <bool OWN>
 __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* __restrict__ u,
                                                      const double* __restrict__ cand, int mode,
                                                      double* __restrict__ rout, double* __restrict__ gamma_out,
@@ -217,13 +219,13 @@ __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* 
       sn[1][v][lane] = u[v * vstride + ir];
     }
   }
-  if (plain && cand && lane < p) {
+  if (!OWN && plain && lane < p) {
     sc[0][lane] = cand[static_cast<int64_t>(A.cell_vtx[e * 2]) * p + lane];
     sc[1][lane] = cand[static_cast<int64_t>(A.cell_vtx[e * 2 + 1]) * p + lane];
   }
   __syncthreads();
   const double h = A.hcell[e], s = 2.0 / h;
-  if (plain && !cand) {
+  if (OWN && plain) {
 #pragma unroll
     for (int l = 0; l < 2; ++l) {
       double acc = 0.0, wsum = 0.0;
@@ -236,32 +238,31 @@ __global__ __launch_bounds__(64) void hp_cell_kernel(SegHPArgs A, const double* 
       if (lane < p) sc[l][lane] = acc / wsum;
     }
   }
-  if (A.cg && lane < n1) {
-    const int a = lane, side = a == 0 ? 0 : 1;
-    const bool shared = (a == 0 || a == p) && (side == 0 ? en[0] : en[1]) >= 0;
-    double g[3] = {0.0, 0.0, 0.0}, go[3] = {0.0, 0.0, 0.0};
-    for (int j = 0; j < n1; ++j) {
-      const double d = A.tab[o.DN + a * n1 + j];
-#pragma unroll
-      for (int v = 0; v < 3; ++v)
-        if (v < nv) g[v] = fma(d, su[v][j], g[v]);
-    }
-    if (shared)
+  if (A.cg) {
+    // lanes 0..p: the own nodes; p + 1 and p + 2: the left and right neighbour's
+    // node at the shared vertex
+    const int side = lane == 0 || lane == n1 ? 0 : 1;
+    const bool nbr = lane >= n1;
+    const int a = !nbr ? lane : (side == 0 ? p : 0);
+    double g[3] = {0.0, 0.0, 0.0};
+    if (lane < n1 + 2)
       for (int j = 0; j < n1; ++j) {
-        const double d = A.tab[o.DN + (p - a) * n1 + j];
+        const double d = A.tab[o.DN + a * n1 + j];
 #pragma unroll
         for (int v = 0; v < 3; ++v)
-          if (v < nv) go[v] = fma(d, sn[side][v][j], go[v]);
+          if (v < nv) g[v] = fma(d, nbr ? sn[side][v][j] : su[v][j], g[v]);
       }
+    const bool shared = (lane == 0 || lane == p) && (side == 0 ? en[0] : en[1]) >= 0;
 #pragma unroll
     for (int v = 0; v < 3; ++v) {
       if (v >= nv) break;
+      const double go = __shfl(g[v], n1 + side, 64);
       double r = g[v] * s;
       if (shared) {                       // ascending cell order
         const double w = 2.0 / (side == 0 ? hn[0] : hn[1]);
-        r = ((side == 0 ? first[0] : first[1]) ? fma(go[v], w, r) : fma(g[v], s, go[v] * w)) / 2.0;
+        r = ((side == 0 ? first[0] : first[1]) ? fma(go, w, r) : fma(g[v], s, go * w)) / 2.0;
       }
-      spg[v][a] = r;
+      if (lane < n1) spg[v][lane] = r;
     }
   }
   __syncthreads();
@@ -475,8 +476,8 @@ cvw_status seghp_eval(const cvw_mesh* m, const cvw_params* prm, int mode, const 
                       double* rcell, double* R, double* gamma, double* alpha, uint32_t* status, hipStream_t s,
                       const LineStage& lst) {
   const SegHPArgs A = seghp_args(m, prm);
-  hipLaunchKernelGGL(hp_cell_kernel, dim3(static_cast<unsigned>(m->E)), dim3(64), 0, s, A, u, cand, mode,
-                     A.cg ? rcell : R, gamma, alpha, status, static_cast<const double*>(lst.un), m->d_dinv_d, lst.a0,
+  hipLaunchKernelGGL(cand ? hp_cell_kernel<false> : hp_cell_kernel<true>, dim3(static_cast<unsigned>(m->E)), dim3(64),
+                     0, s, A, u, cand, mode, A.cg ? rcell : R, gamma, alpha, status, static_cast<const double*>(lst.un), m->d_dinv_d, lst.a0,
                      lst.b0, lst.dt);
   if (A.cg && mode != MODE_SENSOR && R)      // R null: the caller takes the element rows
     hipLaunchKernelGGL(hp_assemble_kernel, dim3(nbh(m->ndof, 256)), dim3(256), 0, s, A, rcell, R);
