@@ -373,6 +373,18 @@ __global__ __launch_bounds__(256) void stage_update_kernel(const Real* __restric
 // stride order, then a fixed tree.
 constexpr int SMALL_THREADS = 1024;
 
+__device__ __forceinline__ double wg_sum(double v, double* sh) {
+  __syncthreads();
+  sh[threadIdx.x] = v;
+  __syncthreads();
+#pragma unroll
+  for (int s = SMALL_THREADS / 2; s > 0; s >>= 1) {
+    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
+    __syncthreads();
+  }
+  return sh[0];
+}
+
 template <typename Real>
 __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
     const Real* __restrict__ b, Real* __restrict__ x, Real* __restrict__ r, Real* __restrict__ z,
@@ -406,7 +418,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
     p[i] = zi;
     d += static_cast<double>(bi) * static_cast<double>(zi);
   }
-  double rz = tree_sum<SMALL_THREADS>(d, sh);
+  double rz = wg_sum(d, sh);
   const double rz0 = rz;
   bool done = !(rz > 0.0);
   for (int it = 0; it < maxit && !done; ++it) {
@@ -425,7 +437,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
       Ap[I] = s;
       d += static_cast<double>(p[I]) * static_cast<double>(s);
     }
-    const double al = rz / tree_sum<SMALL_THREADS>(d, sh);
+    const double al = rz / wg_sum(d, sh);
     d = 0.0;
     for (int64_t i = tid; i < n; i += SMALL_THREADS) {
       x[i] = fma(static_cast<Real>(al), p[i], x[i]);
@@ -435,7 +447,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
       z[i] = zi;
       d += static_cast<double>(ri) * static_cast<double>(zi);
     }
-    const double rzn = tree_sum<SMALL_THREADS>(d, sh);
+    const double rzn = wg_sum(d, sh);
     const double be = rzn / rz;
     rz = rzn;
     if (!(rzn > tol2 * rz0)) { done = true; break; }
