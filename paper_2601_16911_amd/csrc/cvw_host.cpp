@@ -2387,6 +2387,8 @@ cvw_status cvw_sensor(const cvw_mesh* m, const cvw_params* prm, const void* u, v
                      learned_gamma_of(prm, w));
 }
 
+static constexpr int64_t LIMIT_LISTED_CELLS = 1 << 18;
+
 cvw_status cvw_limit(const cvw_mesh* m, const cvw_params* prm, const void* u, void* u_out, double threshold,
                      void* gamma_out, void* ws, size_t ws_bytes, void* stream) {
   cvw_status st = check_common(m, prm, ws_bytes, 2, ws);
@@ -2447,9 +2449,17 @@ cvw_status cvw_limit(const cvw_mesh* m, const cvw_params* prm, const void* u, vo
   // candidates.  The other candidates follow inside the limiter, where they
   // are needed; every candidate is taken from the state before the
   // reconstruction writes, so u_out may be u.
+  // A scalar state on the fused pass: its candidates everywhere, unless the
+  // vertex pass is dear enough to pay for marking and listing the vertices (two
+  // launches more).  Few or nearly all cells selected, in place, listed against
+  // everywhere: P3 400^2 27 / 36 and 27 / 38 us, 550^2 39 / 40 and 45 / 47, 900^2
+  // 46 / 62 and 70 / 80; P2 550^2 27 / 41 and 24 / 36, 900^2 30 / 70 and 43 / 65;
+  // 100^2, any degree, 27 and 23.
   const bool tile = use_tile(m, prm);
+  const bool listed = tile && (nv > 1 || (m->degree == 3 && m->E >= LIMIT_LISTED_CELLS));
   if (tile) {
     if ((st = dgquad_sensor_tile(m, prm, uf, gam, s)) != CVW_OK) return st;
+    if (!listed && (st = dgquad_candidates(m, prm, uf, cand, s)) != CVW_OK) return st;
   } else if ((st = dgquad_candidates(m, prm, uf, cand, s)) != CVW_OK ||
              (st = dgquad_eval(m, prm, MODE_SENSOR, uf, nullptr, nullptr, gam, nullptr, cand, w.status, 0.f, 0.f,
                                0.f, s)) != CVW_OK) {
@@ -2462,7 +2472,7 @@ cvw_status cvw_limit(const cvw_mesh* m, const cvw_params* prm, const void* u, vo
     ln.xi[i] = x[i];
     ln.w[i] = wq[i];
   }
-  return dgquad_limit(m, prm, uf, static_cast<float*>(u_out), cand, tile ? 0 : 1, gam, ln, threshold, count, list,
+  return dgquad_limit(m, prm, uf, static_cast<float*>(u_out), cand, listed ? 0 : 1, gam, ln, threshold, count, list,
                       vflag, vlist, s);
 }
 
