@@ -482,7 +482,8 @@ size_t cvw_batch_workspace_bytes(const cvw_batch* batch);
 cvw_status cvw_batch_step(cvw_batch* batch, int n_steps, int use_graph, void* ws, size_t ws_bytes, void* stream);
 
 /* Blocks per work list (degree, or degree and flux) of the batched kernels,
- * each walking a run of items; <= 0 selects the built-in number.  Results do
+ * rounded up to a multiple of 8, each walking a run of items; <= 0 selects the
+ * built-in number.  Results do
  * not depend on it.  Invalidates a captured graph. */
 cvw_status cvw_batch_set_grid(cvw_batch* batch, int blocks);
 

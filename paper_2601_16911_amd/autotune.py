@@ -2,14 +2,16 @@
 
 The knobs are the blocks per launch of the DG quadrilateral cell pass
 (cvw_mesh_set_grid: each block walks a contiguous run of 16- or 64-cell tiles)
-and of the batched work-list kernels (cvw_batch_set_grid).  Results do not
-depend on them; the tuner checks that every candidate reproduces the first
+and the blocks per work list of the batched kernels (cvw_batch_set_grid).
+Results do not depend on them; the tuner checks that every candidate reproduces the first
 candidate's output bit for bit before it keeps a timing.
 
-The choice is cached in a JSON file keyed by (device architecture, degree,
-space, nodes per cell, flux (which also fixes the number of variables), cell
-count), so a later run with the same workload applies it without timing
-(`params` is the struct from cvw.make_params):
+The choice is cached in a JSON file keyed by what the number means (blocks per
+launch of the cell pass: `mesh`, per work list of a batch: `batch-lists`) and
+the workload (device architecture, degree, space, nodes per cell, flux (which
+also fixes the number of variables), cell count), so a later run with the same
+workload applies it without timing (`params` is the struct from
+cvw.make_params):
 
     best = tune_mesh(mesh, params, u, cand, ws)        # times, caches, applies
     apply_cached(mesh, params)                          # applies a cached choice
@@ -45,7 +47,8 @@ def mesh_key(mesh, params) -> str:
 
 
 def batch_key(batch) -> str:
-    return f"{arch()}|batch|{batch.signature()}"
+    # entries under "batch" hold blocks per launch over all lists, another quantity
+    return f"{arch()}|batch-lists|{batch.signature()}"
 
 
 def load_cache(path: str | None = None) -> dict:
