@@ -28,6 +28,7 @@
 // exchanges nodal values and quadrature terms through LDS and reduces with
 // cross-lane shuffles; idle lanes of a Q_2 team carry zeros.
 #include "cvw_device.h"
+#include <cfloat>
 #include "cvw_cells3d.h"
 
 namespace cvw {
@@ -748,7 +749,7 @@ __device__ __forceinline__ void qspread3(float& r0, float& r1, float& r2, float 
 // c evaluates the three points of plane c; z faces: the three points (p, q = c),
 // with the nodes of the cell and its neighbour on those lines read from memory
 // in that order.  Bound by VALU issue (5300 instructions per wavefront, two
-// wavefronts per SIMD at 225 registers; three would spill).  201,666 cells,
+// wavefronts per SIMD at 231 registers; three would spill).  201,666 cells,
 // Euler: 138 us against 371 with a lane per node and LDS exchange, which
 // waits on 47 loads and 150 LDS operations per two cells.
 template <int FLUX>
@@ -844,7 +845,7 @@ __global__ __launch_bounds__(64) void hex_plane_kernel(const float* __restrict__
     for (int j = 0; j < N1; ++j) d2z[j] = tab->D2[tc][j];
     ddz(uv[0], dz, gz);
     ddz(uv[0], d2z, h);
-    float Sv = 0.0f, Tv = 0.0f;
+    float Sv = 0.0f, Tv = 0.0f, am = 0.0f;
 #pragma unroll
     for (int i = 0; i < NN; ++i) {
       gx[i] = ddx(uv[0], i);
@@ -874,11 +875,13 @@ __global__ __launch_bounds__(64) void hex_plane_kernel(const float* __restrict__
       const float W = Wab[i] * Wc;
       Sv = fmaf(W, f, Sv);
       Tv = fmaf(W * at, f, Tv);
+      am = fmaxf(am, at);
       gs[i] = at;
     }
     Sv = quad_sum(tl < 3 ? Sv : 0.0f);
     Tv = quad_sum(tl < 3 ? Tv : 0.0f);
-    const bool act = Sv > 0.0f && Tv > 0.0f;
+    // alpha~ beyond the float range (|u| from 1e18 on): no weights
+    const bool act = Sv > 0.0f && Tv > 0.0f && quad_max(am) <= FLT_MAX;
     const float q = Sv / Tv;
 #pragma unroll
     for (int i = 0; i < NN; ++i) gs[i] = act ? gs[i] * q : 1.0f;
