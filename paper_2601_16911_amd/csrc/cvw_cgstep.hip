@@ -462,9 +462,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void pcg_line_kernel(
 // `own` consecutive vertices of the chain with 2^levels - 1 more on either side,
 // which is as far as `levels` steps of cyclic reduction reach: blocks need nothing
 // from each other and the whole solve with the stage update is one launch.
-// Float64 throughout.  A NaN among the element rows of a variable leaves its x = 0,
-// an infinity makes it NaN everywhere, as in the conjugate gradient iteration: a
-// single block sees every row, several take the cell kernel's word (rows).
+// Float64 throughout.  A NaN in a variable's assembled right-hand side leaves its
+// x = 0, an infinity makes it NaN everywhere, as in the conjugate gradient
+// iteration.  A single block sees every entry; several take the cell kernel's
+// word on the element rows (rows), and where those hold infinities look for
+// vertices at which two of them meet to a NaN.
 // 128 cells, P2: 4.0 us against 65.3 us for the conjugate gradients (and their
 // assembly and update launches); a step of P1 advection on 1500 cells 37.8 against
 // 563 us, of P4 Euler on 1000 cells 90.6 against 867 us.
@@ -486,7 +488,6 @@ __global__ __launch_bounds__(T) void line_mass_kernel(
   __shared__ double sh[2][T];
   const int t = threadIdx.x, n1 = deg + 1, ni = deg - 1, H = (1 << levels) - 1;
   const int64_t k0 = static_cast<int64_t>(blockIdx.x) * own;
-  uint32_t fl = gridDim.x > 1 ? rows[blockIdx.y] : 0;
   const int64_t off = blockIdx.y * ndof;
   rcell += blockIdx.y * E * n1;
   us += off;
@@ -495,6 +496,16 @@ __global__ __launch_bounds__(T) void line_mass_kernel(
   int64_t k = k0 - H + t;
   if (loop) k = ((k % nv) + nv) % nv;
   const bool in = k >= 0 && k < nv;
+  uint32_t fl = gridDim.x > 1 ? rows[blockIdx.y] : 0;
+  if (fl == CG_ROWS_INF) {                // the same in every block and thread
+    for (int64_t v = t; v < nv; v += T) {
+      const int64_t l = v > 0 ? v - 1 : (loop ? nv - 1 : -1);
+      Real b = Real(0);
+      if (v < E) b += rcell[static_cast<int64_t>(chain[v]) * n1];
+      if (l >= 0) b += rcell[static_cast<int64_t>(chain[l]) * n1 + deg];
+      if (isnan(b)) fl |= CG_ROWS_NAN;
+    }
+  }
   double al[ML], ga[ML], g = 0.0, ib = 0.0;
 #pragma unroll
   for (int l = 0; l < ML; ++l) {
@@ -507,10 +518,11 @@ __global__ __launch_bounds__(T) void line_mass_kernel(
   if (in) {
     ib = red[2 * levels * nv + k];
     const int64_t kl = k > 0 ? k - 1 : (loop ? nv - 1 : -1);
+    Real b = Real(0);                     // the vertex's assembled entry
     if (k < E) {                          // the cell on the right: its node 0
       const Real* r = rcell + static_cast<int64_t>(chain[k]) * n1;
       double s = r[0];
-      fl |= row_bits(s);
+      b += r[0];
       for (int i = 0; i < ni; ++i) {
         const double v = r[i + 1];
         fl |= row_bits(v);
@@ -521,10 +533,11 @@ __global__ __launch_bounds__(T) void line_mass_kernel(
     if (kl >= 0) {                        // the cell on the left: its node p
       const Real* r = rcell + static_cast<int64_t>(chain[kl]) * n1;
       double s = r[deg];
-      fl |= row_bits(s);
+      b += r[deg];
       for (int i = 0; i < ni; ++i) s -= tab[ni + i] * static_cast<double>(r[i + 1]);
       g += s;
     }
+    fl |= row_bits(b);
   }
   sh[0][t] = g;
   fl = (__syncthreads_or(fl & CG_ROWS_NAN) ? CG_ROWS_NAN : 0) | (__syncthreads_or(fl & CG_ROWS_INF) ? CG_ROWS_INF : 0);
