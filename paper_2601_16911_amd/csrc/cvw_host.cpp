@@ -1744,7 +1744,7 @@ cvw_status cvw_mesh_build(const cvw_mesh_desc* d, cvw_mesh** out) {
   if ((st = upload(&m->d_vtx_ptr, ptr32)) != CVW_OK) { free_mesh(m); return st; }
   if ((st = upload(&m->d_vtx_ent, ent)) != CVW_OK) { free_mesh(m); return st; }
   if ((st = upload(&m->d_cell_vtx, m->h_cell_vtx)) != CVW_OK) { free_mesh(m); return st; }
-  {
+  if (d->cell != CVW_SEG) {            // lines: d_line_nb
     // device neighbour table: boundary face b (ascending (cell, face)) as -(b + 1)
     std::vector<int32_t> dn(m->h_nbr);
     int32_t b = 0;
@@ -2039,25 +2039,22 @@ static bool has_stage(const cvw_mesh* m) {
 // float64 scratch of the totals: block partials of up to four variables and the results
 constexpr size_t TOT_SCRATCH = (4 * 1024 + 4) * sizeof(double) + 224;
 
-// CG scratch: P_h grad u (2D: two components; 1D: one per variable) and the
-// element rows of every variable
-static size_t pg_elems(const cvw_mesh* m, const cvw_params* prm) {
-  return static_cast<size_t>(std::max(2, n_var(m, prm->flux))) * m->ndof;
+// CG scratch: on quadrilaterals P_h grad u (two components; the line kernels form
+// P_h u' themselves), the element rows of every variable, and where the mass is
+// inverted by conjugate gradients the right-hand side R, the vectors x, r, z, p,
+// Ap of every variable, the block partials and the scalars
+static size_t pg_elems(const cvw_mesh* m) {
+  return m->space == CVW_CG && m->cell == CVW_QUAD ? 2 * static_cast<size_t>(m->ndof) : 0;
 }
 static size_t rcell_elems(const cvw_mesh* m, const cvw_params* prm) {
-  return static_cast<size_t>(n_var(m, prm->flux)) * m->E * m->nloc;
+  return m->space == CVW_CG ? static_cast<size_t>(n_var(m, prm->flux)) * m->E * m->nloc : 0;
 }
+static bool mass_by_pcg(const cvw_mesh* m) { return m->space == CVW_CG && m->n_mass > 0 && m->line_levels < 0; }
 
 static size_t cg_extra(const cvw_mesh* m, const cvw_params* prm, size_t es) {
-  size_t b = 0;
-  if (m->space == CVW_CG) b += align256(pg_elems(m, prm) * es) + align256(rcell_elems(m, prm) * es);
-  if (m->n_mass > 0) {
-    // stage right-hand side R, and for CG the PCG vectors x, r, z, p, Ap (every
-    // variable) and its block partials and scalars
-    b += align256(state_elems(m, n_var(m, prm->flux)) * es);
-    if (m->space == CVW_CG)
-      b += 5 * align256(state_elems(m, n_var(m, prm->flux)) * es) + align256((pcg_partials(m->ndof) + 8) * sizeof(double));
-  }
+  size_t b = align256(pg_elems(m) * es) + align256(rcell_elems(m, prm) * es);
+  if (mass_by_pcg(m))
+    b += 6 * align256(state_elems(m, n_var(m, prm->flux)) * es) + align256((pcg_partials(m->ndof) + 8) * sizeof(double));
   return b;
 }
 
@@ -2193,10 +2190,9 @@ struct WS {
   uint32_t* status;
   double* tot;                     // totals scratch
   void* cand;
-  void* pg;
-  void* rcell;
-  void* rhs;                       // stage right-hand side (R)
-  void* x, *r, *z, *p, *Ap;        // PCG vectors (CG)
+  void* pg;                        // CG quadrilaterals
+  void* rcell;                     // CG
+  void* rhs, *x, *r, *z, *p, *Ap;  // PCG: right-hand side (R) and vectors, one after another
   double* part;                    // PCG block partials, followed by its 8 scalars
   double* S;
   uint16_t* feat;                  // learned sensor: features [E][48], tile flags, audit partials and results
@@ -2219,25 +2215,19 @@ static WS carve(const cvw_mesh* m, const cvw_params* prm, void* ws) {
     w.cand = p;
     p += align256(static_cast<size_t>(m->nk) * m->Nv * es);
   }
-  if (m->space == CVW_CG) {
-    w.pg = p;
-    p += align256(pg_elems(m, prm) * es);
-    w.rcell = p;
-    p += align256(rcell_elems(m, prm) * es);
-  }
-  if (m->n_mass > 0) {
-    w.rhs = p;
-    p += align256(state_elems(m, n_var(m, prm->flux)) * es);
-    if (m->space == CVW_CG) {
-      void** vecs[5] = {&w.x, &w.r, &w.z, &w.p, &w.Ap};
-      for (void** v : vecs) {
-        *v = p;
-        p += align256(state_elems(m, n_var(m, prm->flux)) * es);
-      }
-      w.part = reinterpret_cast<double*>(p);
-      w.S = w.part + pcg_partials(m->ndof);
-      p += align256((pcg_partials(m->ndof) + 8) * sizeof(double));
+  w.pg = p;
+  p += align256(pg_elems(m) * es);
+  w.rcell = p;
+  p += align256(rcell_elems(m, prm) * es);
+  if (mass_by_pcg(m)) {
+    void** vecs[6] = {&w.rhs, &w.x, &w.r, &w.z, &w.p, &w.Ap};
+    for (void** v : vecs) {
+      *v = p;
+      p += align256(state_elems(m, n_var(m, prm->flux)) * es);
     }
+    w.part = reinterpret_cast<double*>(p);
+    w.S = w.part + pcg_partials(m->ndof);
+    p += align256((pcg_partials(m->ndof) + 8) * sizeof(double));
   }
   if (prm->sensor == CVW_SENSOR_LEARNED) {
     w.feat = reinterpret_cast<uint16_t*>(p);
@@ -2568,7 +2558,7 @@ cvw_status generic_stage(const cvw_mesh* m, const cvw_params* prm, const WS& w, 
   cvw_status st;
   // the direct line solve and the quadrilaterals' conjugate gradients start from
   // the element rows; the line's conjugate gradients need them assembled
-  const bool direct = m->cell == CVW_SEG && m->space == CVW_CG && m->line_levels >= 0;
+  const bool direct = !mass_by_pcg(m);
   const bool quad = m->cell == CVW_QUAD;
   Real* rhs = direct || quad ? nullptr : static_cast<Real*>(w.rhs);
   if (m->cell == CVW_SEG && m->space == CVW_DG)        // diagonal mass: the cell kernel updates the state

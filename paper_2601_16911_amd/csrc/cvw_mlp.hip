@@ -234,12 +234,12 @@ __global__ __launch_bounds__(256) void mlp_train_kernel(const uint16_t* __restri
   __shared__ float sD1f[MLP_HID][33], sD2f[MLP_HID][33], sH2f[MLP_HID][33], sd3[32], sz[4][32];
   __shared__ u32x4 sB[2][2][2][64];      // operand fragments [hi / lo][t][kb][lane]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
-  const int ti = wave & 1, kq = wave >> 1, v0 = 8 * kq;
+  const int ti = wave & 1, kq = wave >> 1;
   const int sglob = blockIdx.x * 32 + c;
   const bool ok = sglob < batch;
   const int64_t row = ok ? idx[sglob] : 0;
   float* out = part + static_cast<int64_t>(blockIdx.x) * MLP_NPARAM;
-  auto unit = [&](int i) { return 32 * ti + 16 * kq + 8 * (i >> 2) + 4 * g + (i & 3); };   // acc_row(v0 + i, g) of tile ti
+  auto unit = [&](int i) { return 32 * ti + 16 * kq + 8 * (i >> 2) + 4 * g + (i & 3); };   // acc_row(8 kq + i, g) of tile ti
   auto share = [&](const float* x) {
     uint16_t hi[8], lo[8];
 #pragma unroll
