@@ -483,8 +483,7 @@ cvw_status cvw_batch_step(cvw_batch* batch, int n_steps, int use_graph, void* ws
 
 /* Blocks per work list (degree, or degree and flux) of the batched kernels,
  * rounded up to a multiple of 8, each walking a run of items; <= 0 selects the
- * built-in number.  Results do
- * not depend on it.  Invalidates a captured graph. */
+ * built-in number.  Results do not depend on it.  Invalidates a captured graph. */
 cvw_status cvw_batch_set_grid(cvw_batch* batch, int blocks);
 
 /* As cvw_poll_status, for the status word of a batch workspace. */

@@ -72,11 +72,17 @@ __device__ __forceinline__ double partial_sum(const double* __restrict__ part, i
 //   apply:  cells and gather in one, every DOF evaluating its rows of its cells;
 //   update.
 // Apply has four times the vector memory instructions (12.7 us at 262 k DOFs against
-// 4.4 + 3.3 us for cells and gather), but where a kernel takes less than its launch
-// one launch less is what counts.  Above PCG_FUSED_PARTIALS partials summing them
-// in every block would cost more than a launch of its own.  Every sum keeps its
-// order: all variants give the same bits.  A step (three stages) at 256 x 256 Q2:
-// 3371 us with six launches per iteration, 980 us now; at 31 x 27: 3591 us and
+// 4.4 + 3.3 us for cells and gather) and one launch less, which counts twice: the
+// iterations after the last active one are launches alone (a step of nothing but
+// those 690 us against 950).  A Q2 step, apply against cells + gather: 128^2 cells
+// 753 and 755 us, 181^2 892 and 859, 222^2 1053 and 980, 300^2 1514 and 1274, 512^2
+// 3959 and 2614; Q1 from 181^2 to 512^2 within 3 %.  The line is at 262,144 DOFs:
+// there (256^2 Q2) steps one after another, which hide the launches, take 1002 us
+// with apply and 964 without, a step that is waited for 1032 and 1120; above, the
+// kernels decide, below, the launches.  Above PCG_FUSED_PARTIALS partials summing
+// them in every block would cost more than a launch of its own.  Every sum keeps
+// its order: all variants give the same bits.  A step (three stages) at 256 x 256
+// Q2: 3371 us with six launches per iteration, 997 us now; at 31 x 27: 3591 us and
 // 697 us; at 500 x 400: 3832 us and 2088 us.
 // ---------------------------------------------------------------------------
 constexpr int PCG_APPLY_PARTIALS = 1024, PCG_FUSED_PARTIALS = 4096;
@@ -597,7 +603,9 @@ cvw_status line_pcg(const cvw_mesh* m, const Real* b, Real* x, Real* r, Real* z,
 // Iterations after which conjugate gradients must have met the tolerance: in
 // the energy norm they reduce the error by 2 ((sqrt(c) - 1) / (sqrt(c) + 1))^k, and
 // the preconditioned residual norm differs from it by a factor sqrt(c) at most
-// (c: the condition number); a tenth and two more for rounding.
+// (c: the condition number); a tenth and two more for rounding.  In float32, over
+// jitters to 0.45, aspects to 1000 and rough right-hand sides, 11 to 23 were needed
+// of 30 and more (Q1), 15 to 19 of 25 and more (Q2).
 static int pcg_iterations(double cond, double tol, int maxit) {
   if (!(cond > 1.0)) return maxit;
   const double q = std::sqrt(cond), k = std::log(2.0 * q / tol) / std::log((q + 1.0) / (q - 1.0));

@@ -1070,9 +1070,11 @@ cvw_status hex_candidates(const cvw_mesh* m, const cvw_params* prm, const float*
 }
 
 // From this many Q_2 cells on the quad-per-cell pass: it has an eighth of the
-// wavefronts, each eight times as long.  Step, Euler, lane per node against
-// quad per cell: 12^3 cells 94 and 106 us, 16^3 106 and 117, 24^3 183 and 129,
-// 32^3 283 and 215 (advection: 81 and 82, 106 and 95, 133 and 100 from 16^3).
+// wavefronts, each eight times as long.  Step, lane per node against quad per
+// cell: advection 16^3 cells 77 and 80 us, 18^3 (5832) 79 and 82, 19^3 (6859) 84
+// and 82, 24^3 95 and 85; Burgers the same to 1 us; Euler 16^3 94 and 105, 17^3
+// (4913) 109 and 109, 18^3 110 and 110, 19^3 119 and 111, 24^3 182 and 121.  One
+// line for all laws: the scalar crossing, up to which Euler loses nothing.
 constexpr int64_t HEX_PLANE_CELLS = 6144;
 template <int P, int FLUX>
 static void launch_hex_eval(const cvw_mesh* m, const MethodScalars& ms, int mode, const float* u, const float* u0,

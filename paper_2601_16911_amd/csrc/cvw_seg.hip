@@ -6,9 +6,9 @@
 //
 //  * seg_vertex_kernel   -- Hermite data D^k u_h^e at the vertex from the two
 //    cells sharing it, Jiang-Shu weights, vertex candidate (eq. taylorcand),
-//    for callers that ask for the candidates themselves;
+//    with general exponents and for callers that ask for the candidates;
 //  * seg_cell_kernel     -- the candidates of the cell's two vertices (unless
-//    the caller gives them), CG: P_h u' at its nodes (nodal average), element
+//    they are given), CG: P_h u' at its nodes (nodal average), element
 //    semi-norms, WENO weights, gamma_e, lambda_e, nu_e, alpha_q and the element
 //    residual (volume + DG interface terms), DG: the stage update (diagonal
 //    mass);

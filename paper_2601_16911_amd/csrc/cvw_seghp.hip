@@ -16,9 +16,10 @@
 //    the vertex, pointwise smoothness indicator (eq. pointsnorm), Jiang-Shu
 //    weights and the vertex candidate (eq. taylorcand).  The patch of an end
 //    vertex is its one cell.
-//    Only for callers that ask for the candidates themselves.
+//    On long lines, at high degree, with general exponents and for callers
+//    that ask for the candidates.
 //  * hp_cell_kernel     -- the candidates of the cell's two vertices (unless
-//    the caller gives them), CG: P_h u' at its nodes, both from the values of
+//    they are given), CG: P_h u' at its nodes, both from the values of
 //    the cell and its two neighbours in LDS (a launch costs more than
 //    evaluating the neighbours again: DG P8 on 4096 cells, Euler, a step of 9
 //    launches 145.6 us, of 3 launches 124.4 us); element semi-norms of the cell and of its two

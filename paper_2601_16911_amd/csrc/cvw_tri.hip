@@ -423,8 +423,9 @@ constexpr int TRI_EVAL_THREADS = 128;
 // issue (half of it float64) and the waits for the scalar loads of the tables:
 // two volume points and four moment points at a time, and for the scalar laws
 // at P = 3 three wavefronts per SIMD (180 registers made two), 99 us against
-// 109 (KPP, 524,288 cells).  The Euler variants spill at that bound (96 us
-// against 80 on 84,000 cells) and keep their registers.
+// 109 (KPP, 524,288 cells).  At that bound the scalar variants spill a little
+// (36 to 52 bytes of scratch per lane) and gain all the same; the Euler variants
+// lose (96 us against 80 on 84,000 cells) and keep their registers.
 template <int P, int FLUX, bool OPEN>
 __global__ __launch_bounds__(TRI_EVAL_THREADS, P == 3 && FLUX != CVW_EULER ? 3 : 1) void tri_eval_kernel(const float* __restrict__ u, const float* __restrict__ u0,
                                                        float* __restrict__ out, float* __restrict__ gamma_out,
